@@ -420,12 +420,31 @@ __global__ void k_mlp_pack(const float* master, MlpPacked* P) {
   if (i < kMlpParams) pack_one(P, i, master[i]);
 }
 
-__global__ void k_mlp_reduce(const float* partial, int rows, int64_t batch, float* grad_out, float* loss_out,
-                             float* master, float* m, float* v, MlpPacked* P, int adam, AdamArgs a) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= kGradRow) return;
+// Sum of the partial rows, kReduceCols columns per block.  The pass has few
+// columns (4418) and, at the training batch of 16,384, 512 rows of them, so one
+// thread per column left 17 blocks walking 512 dependent trips each (129 us);
+// here kReduceGroups threads share a column, each adding every
+// kReduceGroups-th row (128-byte row segments, 16 loads in flight per thread),
+// and the block adds the groups in a fixed order in FP64.
+constexpr int kReduceCols = 32, kReduceGroups = 32;
+__global__ void __launch_bounds__(kReduceCols* kReduceGroups)
+    k_mlp_reduce(const float* partial, int rows, int64_t batch, float* grad_out, float* loss_out, float* master,
+                 float* m, float* v, MlpPacked* P, int adam, AdamArgs a) {
+  __shared__ double red[kReduceGroups / 2][kReduceCols];
+  const int col = threadIdx.x % kReduceCols, grp = threadIdx.x / kReduceCols;
+  const int i = blockIdx.x * kReduceCols + col;
   double s = 0.0;
-  for (int r = 0; r < rows; ++r) s += (double)partial[(int64_t)r * kGradRow + i];
+  if (i < kGradRow) {
+#pragma unroll 16
+    for (int r = grp; r < rows; r += kReduceGroups) s += (double)partial[(int64_t)r * kGradRow + i];
+  }
+  s += __shfl_xor(s, kReduceCols);  // a wave holds two groups of the same columns
+  if ((grp & 1) == 0) red[grp >> 1][col] = s;
+  __syncthreads();
+  if (threadIdx.x >= kReduceCols || i >= kGradRow) return;
+  s = 0.0;
+#pragma unroll
+  for (int g = 0; g < kReduceGroups / 2; ++g) s += red[g][col];
   if (i == kMlpParams) {
     if (loss_out) *loss_out = (float)(s / (double)batch);
     return;
@@ -469,8 +488,8 @@ hipError_t launch_mlp_grad(const MlpPacked* w, const float* x, const float* t, i
 hipError_t launch_mlp_reduce(const float* partial, int rows, int64_t batch, float* grad_out, float* loss_out,
                              float* master, float* m, float* v, MlpPacked* packed, int adam, AdamArgs a,
                              hipStream_t st) {
-  hipLaunchKernelGGL(k_mlp_reduce, dim3((kGradRow + 255) / 256), dim3(256), 0, st, partial, rows, batch, grad_out,
-                     loss_out, master, m, v, packed, adam, a);
+  hipLaunchKernelGGL(k_mlp_reduce, dim3((kGradRow + kReduceCols - 1) / kReduceCols), dim3(kReduceCols * kReduceGroups),
+                     0, st, partial, rows, batch, grad_out, loss_out, master, m, v, packed, adam, a);
   return hipGetLastError();
 }
 
