@@ -253,6 +253,15 @@ __global__ void __launch_bounds__(kGradThreads) k_mlp_grad(const MlpPacked* W, c
   __shared__ __attribute__((aligned(16))) uint16_t lds[kGradThreads / 64][kRows][32];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, h = lane >> 5, col = lane & 31;
   const int64_t tile = (int64_t)blockIdx.x * (kGradThreads / 64) + wv;
+  const int64_t j = tile * 32 + col;
+  const bool ok = j < batch;
+  float f1 = 0.f, f2 = 0.f, tt = 0.f;
+  if (ok) {  // ahead of the parameters: the samples lie anywhere in the data and come from HBM
+    const uint32_t i = batch_index(j, n_data, base, seed_mode, seed, step);
+    f1 = x[2 * (int64_t)i];
+    f2 = x[2 * (int64_t)i + 1];
+    tt = t[i];
+  }
   LaneParams P;
   load_params(W, lane, P);
   bf16x8 w2t[2][4];
@@ -261,15 +270,6 @@ __global__ void __launch_bounds__(kGradThreads) k_mlp_grad(const MlpPacked* W, c
 #pragma unroll
     for (int s = 0; s < 4; ++s) w2t[mt][s] = frag_load(W->w2t[mt][s][lane]);
 
-  const int64_t j = tile * 32 + col;
-  const bool ok = j < batch;
-  float f1 = 0.f, f2 = 0.f, tt = 0.f;
-  if (ok) {
-    const uint32_t i = batch_index(j, n_data, base, seed_mode, seed, step);
-    f1 = x[2 * (int64_t)i];
-    f2 = x[2 * (int64_t)i + 1];
-    tt = t[i];
-  }
   // forward, keeping what the backward pass needs
   bf16x8 hb[4], lb[4];
   float z1[32], s1[32];
@@ -347,7 +347,7 @@ __global__ void __launch_bounds__(kGradThreads) k_mlp_grad(const MlpPacked* W, c
         gw2[a][0] = mfma(af, bh[0], gw2[a][0]);
         gw2[a][1] = mfma(af, bh[1], gw2[a][1]);
       }
-      ge[a] = mfma(af, bx, ge[a]);
+      ge[a] = mfma(bx, af, ge[a]);
     }
   }
 
@@ -360,17 +360,18 @@ __global__ void __launch_bounds__(kGradThreads) k_mlp_grad(const MlpPacked* W, c
     for (int a = 0; a < 2; ++a)
 #pragma unroll
       for (int b = 0; b < 2; ++b) out[kOffW2 + kH * (32 * a + row) + 32 * b + col] = gw2[a][b][r];
-    if (col == 2) {
-      out[kOffB2 + row] = ge[0][r];
-      out[kOffB2 + 32 + row] = ge[1][r];
-      out[kOffB1 + row] = ge[2][r];
-      out[kOffB1 + 32 + row] = ge[3][r];
-    } else if (col < 2) {
-      out[kOffW1 + 2 * row + col] = ge[2][r];
-      out[kOffW1 + 2 * (32 + row) + col] = ge[3][r];
-    } else if (col == 3) {
-      out[kOffW3 + row] = ge[4][r];
-      out[kOffW3 + 32 + row] = ge[5][r];
+  }
+  // the products with (f1, f2, 1, dy) have those as rows 0 to 3 (results 0 to 3
+  // of the lower half wave) and the features as columns: a store per result,
+  // not one masked store per accumulator
+  if (h == 0) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      out[kOffB2 + 32 * b + col] = ge[b][2];
+      out[kOffW1 + 2 * (32 * b + col)] = ge[2 + b][0];
+      out[kOffW1 + 2 * (32 * b + col) + 1] = ge[2 + b][1];
+      out[kOffB1 + 32 * b + col] = ge[2 + b][2];
+      out[kOffW3 + 32 * b + col] = ge[4 + b][3];
     }
   }
   // b3 and the squared residuals: sums over the 32 samples, fixed order
