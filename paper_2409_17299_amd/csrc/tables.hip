@@ -21,6 +21,15 @@
 // Integrals over w use 8-point Gauss-Legendre on panels of fixed width;
 // inverse CDFs invert the cumulative panel sums by Newton iteration inside the
 // panel that holds the target.
+//
+// The build is bound by FP64 arithmetic, nearly all of it in the two Bessel
+// functions: a Newton step of one table entry takes nine of them, and a sum of
+// up to 288 exponentials each time made the default tables 165 ms.  Both are
+// functions of y alone and smooth in ln y once e^-y is taken out, so the sums
+// are taken only at the nodes of piecewise polynomials (k_bessel_table: 688
+// panels, 5,504 sums) and every integrand reads those (16 multiply-adds and an
+// exponential): 165 -> 0.6 ms (k_cdf_rows 109 + 55 -> 0.20 + 0.14, k_rate_nodes
+// 2.0 -> 0.10), the FP32 tables the same and the FP64 ones to 1e-13.
 
 #include <algorithm>
 #include <cmath>
@@ -53,6 +62,7 @@ struct Consts {
   double b23[kBesselN];               // h cosh(2 t_j / 3) (half weight at j = 0)
   double b13[kBesselN];               // h cosh(t_j / 3) / cosh(t_j)
   double k23_small, ki13_zero;        // Gamma(2/3)/2 2^{2/3}, pi/sqrt3
+  double to_power[64];                // [power][node]: values at 8 Chebyshev nodes -> powers
 };
 
 // e^{y_shift} K_{2/3}(y) and e^{y_shift} Ki_{1/3}(y), y_shift <= y (keeps the
@@ -64,6 +74,23 @@ struct Consts {
 // the trapezoid rule in v converges like exp(-pi^2 / h^2).
 constexpr double kBesselHv = 0.25;
 constexpr int kBesselNv = 27;  // v up to 6.5
+
+// term j of the sum in v (y > 4; r2y = 1 / sqrt(2y), iy = 1 / y) and in t
+__device__ __forceinline__ void bessel_term_v(int j, double r2y, double iy, double& s23, double& s13) {
+  const double v = j * kBesselHv;
+  const double a = asinh(v * r2y);
+  const double wv = (j == 0 ? 0.5 : 1.0) * kBesselHv * exp(-v * v) * 2.0 * r2y / sqrt(1.0 + v * v * r2y * r2y);
+  const double c23 = cosh(a * (4.0 / 3.0)), c13 = cosh(a * (2.0 / 3.0));
+  s23 = fma(wv, c23, s23);
+  s13 = fma(wv, c13 / (1.0 + v * v * iy), s13);
+}
+__device__ __forceinline__ void bessel_term_t(const Consts& c, int j, double y, double& s23, double& s13) {
+  const double a = y * c.bc[j];
+  if (a > 745.0) return;
+  const double ej = exp(-a);
+  s23 = fma(c.b23[j], ej, s23);
+  s13 = fma(c.b13[j], ej, s13);
+}
 
 __device__ void bessel_pair(const Consts& c, double y, double y_shift, double& k23, double& ki13) {
   if (y - y_shift > 745.0) {
@@ -80,62 +107,133 @@ __device__ void bessel_pair(const Consts& c, double y, double y_shift, double& k
   double s23 = 0.0, s13 = 0.0;
   if (y > 4.0) {
     const double r2y = 1.0 / sqrt(2.0 * y), iy = 1.0 / y;
-    for (int j = kBesselNv - 1; j >= 0; --j) {
-      const double v = j * kBesselHv;
-      const double a = asinh(v * r2y);
-      const double wv = (j == 0 ? 0.5 : 1.0) * kBesselHv * exp(-v * v) * 2.0 * r2y / sqrt(1.0 + v * v * r2y * r2y);
-      const double c23 = cosh(a * (4.0 / 3.0)), c13 = cosh(a * (2.0 / 3.0));
-      s23 = fma(wv, c23, s23);
-      s13 = fma(wv, c13 / (1.0 + v * v * iy), s13);
-    }
+    for (int j = kBesselNv - 1; j >= 0; --j) bessel_term_v(j, r2y, iy, s23, s13);
   } else {
     // terms with y (cosh t - 1) > 745 underflow
     int jmax = (int)(acosh(1.0 + 745.0 / y) * (1.0 / kBesselH)) + 1;
     jmax = jmax < kBesselN - 1 ? jmax : kBesselN - 1;
-    for (int j = jmax; j >= 0; --j) {  // small terms first
-      const double a = y * c.bc[j];
-      if (a > 745.0) continue;
-      const double ej = exp(-a);
-      s23 = fma(c.b23[j], ej, s23);
-      s13 = fma(c.b13[j], ej, s13);
-    }
+    for (int j = jmax; j >= 0; --j) bessel_term_t(c, j, y, s23, s13);  // small terms first
   }
   k23 = s23 * e;
   ki13 = s13 * e;
 }
 
+// ------------------------------------------------------------------ Bessel functions by interpolation
+// S(w) = e^y K_{2/3}(y) and e^y Ki_{1/3}(y), y = e^{3w}, as polynomials of
+// degree 7 through 8 Chebyshev nodes on panels of kBtDW in w.  In ln y the
+// functions are analytic within +-i pi of the real axis; with a panel's
+// half-width of 3/64 in ln y the interpolation error falls as
+// (2 pi 64 / 3)^-8 = 1e-17.  The table covers y from kYSmall to 8.7e7, past
+// which (the pair spectrum at chi < 3e-8) the sums are taken directly.
+constexpr double kBtDW = 1.0 / 32.0;
+constexpr double kBtW0 = -493.0 / 32.0;  // y = 8.4e-21
+constexpr int kBtPanels = 688;           // up to w = 6.09375, y = 8.7e7
+constexpr int kBtNodes = 8;
+struct BesselTable {
+  double c[kBtPanels][2][kBtNodes];  // ascending powers of v in [-1, 1]
+};
+
+// One wave per panel: eight lanes share a node, each adding every eighth term
+// of its sum; then lane (function, power) forms a coefficient.
+__global__ void __launch_bounds__(64) k_bessel_table(const Consts* cg, BesselTable* out) {
+  const Consts& c = *cg;
+  const int lane = threadIdx.x, node = lane >> 3, part = lane & 7;
+  __shared__ double val[2][kBtNodes];
+  const double v = cos(kPi * (node + 0.5) / kBtNodes);
+  const double y = exp(3.0 * (kBtW0 + kBtDW * (blockIdx.x + 0.5 * (v + 1.0))));
+  double s23 = 0.0, s13 = 0.0;
+  if (y > 4.0) {
+    const double r2y = 1.0 / sqrt(2.0 * y), iy = 1.0 / y;
+    for (int j = part; j < kBesselNv; j += 8) bessel_term_v(j, r2y, iy, s23, s13);
+  } else {
+    for (int j = part; j < kBesselN; j += 8) bessel_term_t(c, j, y, s23, s13);
+  }
+  for (int o = 1; o < 8; o <<= 1) {
+    s23 += __shfl_xor(s23, o);
+    s13 += __shfl_xor(s13, o);
+  }
+  if (part == 0) {
+    val[0][node] = s23;
+    val[1][node] = s13;
+  }
+  __syncthreads();
+  if (lane < 2 * kBtNodes) {
+    const int f = lane / kBtNodes, q = lane % kBtNodes;
+    double acc = 0.0;
+    for (int m = 0; m < kBtNodes; ++m) acc = fma(c.to_power[q * kBtNodes + m], val[f][m], acc);
+    out->c[blockIdx.x][f][q] = acc;
+  }
+}
+
+// e^{y_shift} K_{2/3}(y) and e^{y_shift} Ki_{1/3}(y) at y = e^{3w} (y_shift <= y)
+__device__ __forceinline__ void bessel_at(const Consts& c, const BesselTable* bt, double w, double y, double y_shift,
+                                          double& k23, double& ki13) {
+  const double u = (w - kBtW0) * (1.0 / kBtDW);
+  if (!(u >= 0.0 && u < (double)kBtPanels) || y < kYSmall) {
+    bessel_pair(c, y, y_shift, k23, ki13);
+    return;
+  }
+  if (y - y_shift > 745.0) {
+    k23 = 0.0;
+    ki13 = 0.0;
+    return;
+  }
+  const int k = (int)u;
+  const double v = 2.0 * (u - (double)k) - 1.0;
+  const double2* q = reinterpret_cast<const double2*>(bt->c[k]);
+  double2 a[kBtNodes / 2], b[kBtNodes / 2];
+#pragma unroll
+  for (int i = 0; i < kBtNodes / 2; ++i) {
+    a[i] = q[i];
+    b[i] = q[kBtNodes / 2 + i];
+  }
+  double s23 = a[3].y, s13 = b[3].y;
+#pragma unroll
+  for (int i = 3; i >= 0; --i) {
+    s23 = fma(s23, v, a[i].x);
+    s13 = fma(s13, v, b[i].x);
+    if (i > 0) {
+      s23 = fma(s23, v, a[i - 1].y);
+      s13 = fma(s13, v, b[i - 1].y);
+    }
+  }
+  const double e = exp(-(y - y_shift));
+  k23 = s23 * e;
+  ki13 = s13 * e;
+}
+
 // emission integrand in w (reduced by alpha/gamma)
-__device__ double rad_integrand(const Consts& c, double chi, double w) {
+__device__ double rad_integrand(const Consts& c, const BesselTable* bt, double chi, double w) {
   const double y = exp(3.0 * w);
   const double z = 1.5 * chi * y;
   const double omd = 1.0 / (1.0 + z);
   const double a = omd + (1.0 + z);
   double k23, ki13;
-  bessel_pair(c, y, 0.0, k23, ki13);
+  bessel_at(c, bt, w, y, 0.0, k23, ki13);
   return (a * k23 - ki13) * (1.0 / (kSqrt3 * kPi)) * 4.5 * chi * y * omd * omd;
 }
 
 // pair integrand in w (reduced by alpha/eps), scaled by e^{8/(3 chi)}
-__device__ double pair_integrand(const Consts& c, double chi, double w) {
+__device__ double pair_integrand(const Consts& c, const BesselTable* bt, double chi, double w) {
   const double ch = cosh(w);
   const double y0 = 8.0 / (3.0 * chi);
   const double sh = sinh(0.5 * w);
   const double y = y0 + y0 * sh * sh;  // (4/(3chi))(1 + cosh w) = y0 cosh^2(w/2)
   double k23, ki13;
-  bessel_pair(c, y, y0, k23, ki13);
+  bessel_at(c, bt, log(y) * (1.0 / 3.0), y, y0, k23, ki13);
   return (2.0 * ch * k23 + ki13) * (1.0 / (kSqrt3 * kPi)) / (2.0 * (1.0 + ch));
 }
 
 template <int P>
-__device__ double integrand(const Consts& c, double chi, double w) {
-  return P == 0 ? rad_integrand(c, chi, w) : pair_integrand(c, chi, w);
+__device__ double integrand(const Consts& c, const BesselTable* bt, double chi, double w) {
+  return P == 0 ? rad_integrand(c, bt, chi, w) : pair_integrand(c, bt, chi, w);
 }
 
 template <int P>
-__device__ double gl_panel(const Consts& c, double chi, double a, double b) {
+__device__ double gl_panel(const Consts& c, const BesselTable* bt, double chi, double a, double b) {
   const double m = 0.5 * (a + b), h = 0.5 * (b - a);
   double s = 0.0;
-  for (int i = 0; i < kGL; ++i) s = fma(c.gl_w[i], integrand<P>(c, chi, fma(h, c.gl_x[i], m)), s);
+  for (int i = 0; i < kGL; ++i) s = fma(c.gl_w[i], integrand<P>(c, bt, chi, fma(h, c.gl_x[i], m)), s);
   return s * h;
 }
 
@@ -173,32 +271,30 @@ __device__ double block_sum(double v, double* red) {
 // Reduced rate integral at chi: emission: int over the whole w line;
 // pairs: twice the half line (scaled by e^{8/(3chi)}).
 template <int P>
-__device__ double reduced_total(const Consts& c, double chi, double* red) {
+__device__ double reduced_total(const Consts& c, const BesselTable* bt, double chi, double* red) {
   const Panels pg = panels_for<P>(chi);
   double acc = 0.0;
   for (int k = threadIdx.x; k < npanels<P>(); k += blockDim.x)
-    acc += gl_panel<P>(c, chi, pg.w0 + k * pg.dw, pg.w0 + (k + 1) * pg.dw);
+    acc += gl_panel<P>(c, bt, chi, pg.w0 + k * pg.dw, pg.w0 + (k + 1) * pg.dw);
   double tot = block_sum(acc, red);
-  if (P == 0) tot += integrand<0>(c, chi, kRadW0);  // tail below w0 ~ e^w
+  if (P == 0) tot += integrand<0>(c, bt, chi, kRadW0);  // tail below w0 ~ e^w
   else tot *= 2.0;
   return tot;
 }
 
-__global__ void __launch_bounds__(256) k_rate_nodes(const Consts* cg, int process, double s_lo, double* g_out) {
-  __shared__ Consts c;
+__global__ void __launch_bounds__(256) k_rate_nodes(const Consts* cg, const BesselTable* bt, int process, double s_lo,
+                                                    double* g_out) {
   __shared__ double red[256];
-  for (int i = threadIdx.x; i < (int)(sizeof(Consts) / sizeof(double)); i += blockDim.x)
-    reinterpret_cast<double*>(&c)[i] = reinterpret_cast<const double*>(cg)[i];
-  __syncthreads();
+  const Consts& c = *cg;
   const int seg = blockIdx.x / kChebN, m = blockIdx.x % kChebN;
   const double xm = cos(kPi * (m + 0.5) / kChebN);
   const double s = s_lo + seg * kChebSegWidth + 0.5 * kChebSegWidth * (xm + 1.0);
   const double chi = exp(s);
   double tot;
   if (process == 0)
-    tot = reduced_total<0>(c, chi, red);
+    tot = reduced_total<0>(c, bt, chi, red);
   else
-    tot = reduced_total<1>(c, chi, red);
+    tot = reduced_total<1>(c, bt, chi, red);
   if (threadIdx.x == 0) g_out[blockIdx.x] = log(tot) - s;  // pairs: + 8/(3chi) is in the scaling
 }
 
@@ -232,28 +328,73 @@ __global__ void k_rate_herm(const double* coef, int nseg, double s_lo, int n, do
   out[i] = make_float2((float)g, (float)(h * dg_ds));
 }
 
-// One row of an inverse-CDF grid: chi = exp(s0 + row hs); columns x0 + j hx.
+// Exclusive prefix sum of v >= 0 over the block (kRowThreads threads) in thread
+// order, by additions alone: what lies above a panel is many orders smaller
+// than the panel itself, so nothing is taken off a sum.
+constexpr int kRowThreads = 512;
+__device__ __forceinline__ double block_scan(double v, double* wave_sum) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int o = 1; o < 64; o <<= 1) {
+    const double up = __shfl_up(v, o);
+    if (lane >= o) v += up;
+  }
+  if (lane == 63) wave_sum[wave] = v;
+  const double below = __shfl_up(v, 1);
+  __syncthreads();
+  double before = 0.0;
+  for (int w = 0; w < wave; ++w) before += wave_sum[w];
+  __syncthreads();
+  return lane ? before + below : before;
+}
+
+// A row of an inverse-CDF grid: chi = exp(s0 + row hs); columns x0 + j hx.
+struct GridRows {
+  double s0, x0;
+  double hs32, hx32, hs64, hx64;
+  int rows32, cols32, cols64;
+  float* out32;
+  double* out64;
+};
+// One block per row, the FP32 grid's rows first, then the FP64 grid's (one
+// launch fills the chip: the FP32 grid alone has 70 and 47 rows).
 template <int P>
-__global__ void __launch_bounds__(256) k_cdf_rows(const Consts* cg, double s0, double hs, double x0, double hx,
-                                                  int cols, float* out32, double* out64) {
-  __shared__ Consts c;
+__global__ void __launch_bounds__(kRowThreads) k_cdf_rows(const Consts* cg, const BesselTable* bt, GridRows g) {
+  static_assert(kRadPanels <= 2 * kRowThreads && kPairPanels <= 2 * kRowThreads, "two panels per thread");
   __shared__ double I[kRadPanels];
   __shared__ double C[kRadPanels + 1], D[kRadPanels + 1];
-  for (int i = threadIdx.x; i < (int)(sizeof(Consts) / sizeof(double)); i += blockDim.x)
-    reinterpret_cast<double*>(&c)[i] = reinterpret_cast<const double*>(cg)[i];
-  __syncthreads();
-  const int row = blockIdx.x;
-  const double s = s0 + row * hs;
+  __shared__ double wave_sum[kRowThreads / 64];
+  const Consts& c = *cg;
+  const bool f32 = (int)blockIdx.x < g.rows32;
+  const int row = f32 ? (int)blockIdx.x : (int)blockIdx.x - g.rows32;
+  const int cols = f32 ? g.cols32 : g.cols64;
+  const double hx = f32 ? g.hx32 : g.hx64, x0 = g.x0;
+  float* out32 = f32 ? g.out32 : nullptr;
+  double* out64 = f32 ? nullptr : g.out64;
+  const double s = g.s0 + row * (f32 ? g.hs32 : g.hs64);
   const double chi = exp(s);
   const int np = npanels<P>();
   const Panels pg = panels_for<P>(chi);
-  for (int k = threadIdx.x; k < np; k += blockDim.x) I[k] = gl_panel<P>(c, chi, pg.w0 + k * pg.dw, pg.w0 + (k + 1) * pg.dw);
+  for (int k = threadIdx.x; k < np; k += blockDim.x)
+    I[k] = gl_panel<P>(c, bt, chi, pg.w0 + k * pg.dw, pg.w0 + (k + 1) * pg.dw);
   __syncthreads();
-  if (threadIdx.x == 0) {
-    C[0] = P == 0 ? integrand<0>(c, chi, kRadW0) : 0.0;
-    for (int k = 0; k < np; ++k) C[k + 1] = C[k] + I[k];
-    D[np] = 0.0;
-    for (int k = np - 1; k >= 0; --k) D[k] = D[k + 1] + I[k];
+  // C[k]: the integral below panel k (with the tail below the panels); D[k]:
+  // from panel k to the top.  Thread t holds panels 2t and 2t + 1 (and, for D,
+  // the same counted from the top).
+  {
+    const double c0 = P == 0 ? integrand<0>(c, bt, chi, kRadW0) : 0.0;
+    const int k = 2 * threadIdx.x;
+    const double a = k < np ? I[k] : 0.0, b = k + 1 < np ? I[k + 1] : 0.0;
+    const double up = c0 + block_scan(a + b, wave_sum);
+    if (k < np) C[k + 1] = up + a;
+    if (k + 1 < np) C[k + 2] = up + a + b;
+    const double da = k < np ? I[np - 1 - k] : 0.0, db = k + 1 < np ? I[np - 2 - k] : 0.0;
+    const double down = block_scan(da + db, wave_sum);
+    if (k < np) D[np - 1 - k] = down + da;
+    if (k + 1 < np) D[np - 2 - k] = down + da + db;
+    if (threadIdx.x == 0) {
+      C[0] = c0;
+      D[np] = 0.0;
+    }
   }
   __syncthreads();
   const double total = P == 0 ? C[np] : 2.0 * D[0];
@@ -289,12 +430,20 @@ __global__ void __launch_bounds__(256) k_cdf_rows(const Consts* cg, double s0, d
     double wlo = a, whi = b;
     double w = a + (b - a) * fmin(1.0, fmax(0.0, I[k] > 0.0 ? loc / I[k] : 0.5));
     for (int it = 0; it < 60; ++it) {
-      const double G = gl_panel<P>(c, chi, a, w) - loc;
+      const double G = gl_panel<P>(c, bt, chi, a, w) - loc;
       if (G > 0.0) whi = w; else wlo = w;
-      const double f = integrand<P>(c, chi, w);
+      const double f = integrand<P>(c, bt, chi, w);
       double wn = f > 0.0 ? w - G / f : 0.5 * (wlo + whi);
+      // Newton's error squares: after a step of 1e-8 panels only rounding is
+      // left, so the search ends there.  (Testing the bracket first sent such a
+      // step, which often ends on the bracket itself, back to a bisection, and
+      // most entries ran all 60 trips.)
+      if (f > 0.0 && fabs(wn - w) <= 1e-8 * (b - a)) {
+        w = fmin(fmax(wn, a), b);
+        break;
+      }
       if (!(wn > wlo && wn < whi)) wn = 0.5 * (wlo + whi);
-      const bool done = fabs(wn - w) <= 1e-15 * fmax(1.0, fabs(w)) || whi - wlo <= 1e-15 * fmax(1.0, fabs(w));
+      const bool done = whi - wlo <= 1e-15 * fmax(1.0, fabs(w));
       w = wn;
       if (done) break;
     }
@@ -339,6 +488,22 @@ void gauss_legendre(int n, double* x, double* w) {
   }
 }
 
+// out[q][m]: the weight of the value at Chebyshev node cos(pi (m + 1/2) / n)
+// in the coefficient of power q of the interpolating polynomial.
+void chebyshev_to_power(int n, double* out) {
+  std::vector<std::vector<double>> t(n, std::vector<double>(n, 0.0));  // T_j in powers
+  t[0][0] = 1.0;
+  if (n > 1) t[1][1] = 1.0;
+  for (int j = 2; j < n; ++j)
+    for (int q = 0; q < n; ++q) t[j][q] = (q ? 2.0 * t[j - 1][q - 1] : 0.0) - t[j - 2][q];
+  for (int q = 0; q < n; ++q)
+    for (int m = 0; m < n; ++m) {
+      double a = 0.0;
+      for (int j = 0; j < n; ++j) a += (j ? 2.0 : 1.0) / n * std::cos(kPi * j * (m + 0.5) / n) * t[j][q];
+      out[q * n + m] = a;
+    }
+}
+
 size_t align_up(size_t v) { return (v + 255) & ~size_t(255); }
 
 }  // namespace
@@ -379,6 +544,7 @@ qed_status build_tables(const qed_table_cfg& cfg, hipStream_t stream, qed_tables
     return o;
   };
   const size_t o_consts = take(sizeof(Consts));
+  const size_t o_bessel = take(sizeof(BesselTable));
   size_t o_nodes[2], o_cheb[2], o_herm[2], o_c32[2], o_c64[2];
   for (int p = 0; p < 2; ++p) {
     o_nodes[p] = take(sizeof(double) * g.nseg[p] * kChebN);
@@ -403,15 +569,18 @@ qed_status build_tables(const qed_table_cfg& cfg, hipStream_t stream, qed_tables
   }
   hc.k23_small = 0.5 * std::tgamma(2.0 / 3.0) * std::pow(2.0, 2.0 / 3.0);
   hc.ki13_zero = kPi / kSqrt3;
+  chebyshev_to_power(kBtNodes, hc.to_power);
   Consts* dconsts = reinterpret_cast<Consts*>(base + o_consts);
   SFQED_HIP(hipMemcpyAsync(dconsts, &hc, sizeof(Consts), hipMemcpyHostToDevice, stream));
+  BesselTable* bt = reinterpret_cast<BesselTable*>(base + o_bessel);
+  hipLaunchKernelGGL(k_bessel_table, dim3(kBtPanels), dim3(64), 0, stream, dconsts, bt);
 
   for (int p = 0; p < 2; ++p) {
     double* nodes = reinterpret_cast<double*>(base + o_nodes[p]);
     double* cheb = reinterpret_cast<double*>(base + o_cheb[p]);
     float2* herm = reinterpret_cast<float2*>(base + o_herm[p]);
-    hipLaunchKernelGGL(k_rate_nodes, dim3(g.nseg[p] * kChebN), dim3(256), 0, stream, dconsts, p, g.cheb_s_lo[p],
-                       nodes);
+    hipLaunchKernelGGL(k_rate_nodes, dim3(g.nseg[p] * kChebN), dim3(256), 0, stream, dconsts, bt, p,
+                       g.cheb_s_lo[p], nodes);
     hipLaunchKernelGGL(k_cheb_coeffs, dim3(g.nseg[p]), dim3(32), 0, stream, nodes, g.nseg[p], cheb);
     const double hs = g.nseg[p] * kChebSegWidth / (g.herm_n - 1);
     hipLaunchKernelGGL(k_rate_herm, dim3((g.herm_n + 255) / 256), dim3(256), 0, stream, cheb, g.nseg[p],
@@ -429,17 +598,12 @@ qed_status build_tables(const qed_table_cfg& cfg, hipStream_t stream, qed_tables
     double* c64 = reinterpret_cast<double*>(base + o_c64[p]);
     const double hs32 = (g.s1[p] - g.s0[p]) / (g.rows32[p] - 1), hx32 = (g.x1[p] - g.x0[p]) / (g.cols32[p] - 1);
     const double hs64 = (g.s1[p] - g.s0[p]) / (g.rows64[p] - 1), hx64 = (g.x1[p] - g.x0[p]) / (g.cols64[p] - 1);
-    if (p == 0) {
-      hipLaunchKernelGGL(k_cdf_rows<0>, dim3(g.rows32[p]), dim3(256), 0, stream, dconsts, g.s0[p], hs32, g.x0[p],
-                         hx32, g.cols32[p], c32, (double*)nullptr);
-      hipLaunchKernelGGL(k_cdf_rows<0>, dim3(g.rows64[p]), dim3(256), 0, stream, dconsts, g.s0[p], hs64, g.x0[p],
-                         hx64, g.cols64[p], (float*)nullptr, c64);
-    } else {
-      hipLaunchKernelGGL(k_cdf_rows<1>, dim3(g.rows32[p]), dim3(256), 0, stream, dconsts, g.s0[p], hs32, g.x0[p],
-                         hx32, g.cols32[p], c32, (double*)nullptr);
-      hipLaunchKernelGGL(k_cdf_rows<1>, dim3(g.rows64[p]), dim3(256), 0, stream, dconsts, g.s0[p], hs64, g.x0[p],
-                         hx64, g.cols64[p], (float*)nullptr, c64);
-    }
+    const GridRows gr{g.s0[p], g.x0[p], hs32, hx32, hs64, hx64, g.rows32[p], g.cols32[p], g.cols64[p], c32, c64};
+    const dim3 rows(g.rows32[p] + g.rows64[p]);
+    if (p == 0)
+      hipLaunchKernelGGL(k_cdf_rows<0>, rows, dim3(kRowThreads), 0, stream, dconsts, bt, gr);
+    else
+      hipLaunchKernelGGL(k_cdf_rows<1>, rows, dim3(kRowThreads), 0, stream, dconsts, bt, gr);
     SFQED_HIP(hipGetLastError());
     CdfView& cv = t->view.cdf[p];
     cv.f32 = c32;
