@@ -236,11 +236,22 @@ __device__ __forceinline__ T grid_interp(const P* tab, int rows, int cols, T us,
   T ws[4], wx[4];
   lag4<T>(us - T(i), ws);
   lag4<T>(ux - T(j), wx);
-  T acc = T(0);
+  // All sixteen values are fetched before the first is used (the empty asm
+  // needs them all): left to itself the compiler saves registers by waiting for
+  // each pair in turn, eight LDS or L2 latencies one after another.
+  T g[16];
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
     const P* r = tab + (i - 1 + a) * cols + (j - 1);
-    const T v = wx[0] * (T)r[0] + wx[1] * (T)r[1] + wx[2] * (T)r[2] + wx[3] * (T)r[3];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) g[4 * a + b] = (T)r[b];
+  }
+  asm("" : "+v"(g[0]), "+v"(g[1]), "+v"(g[2]), "+v"(g[3]), "+v"(g[4]), "+v"(g[5]), "+v"(g[6]), "+v"(g[7]));
+  asm("" : "+v"(g[8]), "+v"(g[9]), "+v"(g[10]), "+v"(g[11]), "+v"(g[12]), "+v"(g[13]), "+v"(g[14]), "+v"(g[15]));
+  T acc = T(0);
+#pragma unroll
+  for (int a = 0; a < 4; ++a) {
+    const T v = wx[0] * g[4 * a] + wx[1] * g[4 * a + 1] + wx[2] * g[4 * a + 2] + wx[3] * g[4 * a + 3];
     acc += ws[a] * v;
   }
   return acc;
