@@ -371,6 +371,24 @@ struct EventLog {
   }
 };
 
+// The shape of a lepton count launch: its blocks, and how many waves of each
+// get particles.  A wave's trip takes as long with one lane busy as with 64, so
+// few waves with long queues use the lanes best; more waves per SIMD hide more
+// of each other's latencies.  One wave per SIMD up to 256 particles for each,
+// two up to 512, then four.  Measured with these bounds at 64 / 128, 128 / 256
+// and 256 / 512: 1e5 electrons in a static field 451, 418, 413 us a step, three
+// rotating-field steps from 9e5 particles 2.95, 2.78, 2.70 ms, 2e5 particles in
+// FP64 5.40, 4.91, 4.81 ms; 512 / 512 is no better (414, 2.76, 4.86).
+struct LeptonGrid {
+  int blocks, block_waves;
+};
+LeptonGrid lepton_grid(int64_t n, int num_cu) {
+  const int64_t simds = 4ll * num_cu;
+  if (n <= 256 * simds) return {(int)std::min<int64_t>((n + 255) / 256, num_cu), 4};
+  if (n <= 512 * 2 * simds) return {num_cu, 8};
+  return {2 * num_cu, 8};
+}
+
 // One launch (count, scan, write) over particles [begin, begin + n) of one
 // store.
 template <typename T>
@@ -483,7 +501,13 @@ qed_status run_launch(Scratch* S, hipStream_t st, const qed_tables* tab, const q
            sizeof(float) * tab->view.cdf[p].rows32 * tab->view.cdf[p].cols32;
   // leptons: 2 blocks per CU (the emission tables take ~78 KiB of LDS); photons: 4
   const int max_grid = S->num_cu * (photon ? 4 : 2);
-  const int grid = (int)std::min<int64_t>((n + kStepThreads - 1) / kStepThreads, max_grid);
+  int grid = (int)std::min<int64_t>((n + kStepThreads - 1) / kStepThreads, max_grid);
+  if (!photon) {
+    const LeptonGrid g = lepton_grid(n, S->num_cu);
+    grid = g.blocks;
+    a.block_waves = g.block_waves;
+    a.wq = wq_plan((uint32_t)n, (uint32_t)(g.blocks * g.block_waves));
+  }
 
   ScanArgs s;
   s.counts = S->counts;

@@ -20,7 +20,34 @@ constexpr int kMergedTile = kStepThreads * kMergedItems;
 constexpr int kQueueParts = 8;
 constexpr int kQueueStride = 16;  // 64-bit words between counters: one 128-byte line each
 constexpr int kQueueWords = kQueueParts * kQueueStride;
-constexpr uint64_t kChunkMin = 256, kChunkMax = 8192;
+constexpr uint32_t kChunkMin = 256, kChunkMax = 8192;
+// How a lepton launch of n particles deals them out to its waves (see wq_take):
+// every wave owns `pieces` pieces of `piece` particles, dealt in turn; the last
+// `rest` particles come from the counters.  Up to kOwnMax particles per wave
+// the waves own everything.
+struct WqPlan {
+  uint32_t n, waves, piece, pieces, rest, chunk_div;
+};
+constexpr uint32_t kOwnMax = 512;
+__host__ __device__ inline WqPlan wq_plan(uint32_t n, uint32_t waves) {
+  WqPlan p;
+  p.n = n;
+  p.waves = waves;
+  const uint32_t per = (uint32_t)(((uint64_t)n + waves - 1) / waves);
+  if (per <= kOwnMax) {
+    p.pieces = per <= 64 ? 1 : (per + 63) / 64;
+    const uint64_t all = (uint64_t)waves * p.pieces;
+    p.piece = (uint32_t)((n + all - 1) / all);
+    p.rest = 0;
+  } else {
+    p.piece = 64;
+    p.pieces = per / 128;
+    p.rest = n - waves * p.pieces * 64;
+  }
+  p.chunk_div = 2 * (waves / kQueueParts > 0 ? waves / kQueueParts : 1);
+  return p;
+}
+
 // The lepton write kernel runs one block of kWriteThreads per CU (four waves
 // per SIMD, one copy of the LDS tables).  Its child records are staged per
 // lane in LDS, kLinePieces 16-byte pieces (a 64-byte half line) at a time, and
@@ -102,6 +129,8 @@ struct StepArgs {
   int64_t* offsets;    // [n]
   int32_t* list;       // [n]
   const int64_t* list_len;
+  WqPlan wq;            // leptons: how the count pass deals out its particles
+  int32_t block_waves;  // and how many waves of each block get any
   unsigned long long* queue;  // work counters of the count, then the write kernel: 2 x kQueueWords, zero at launch
   unsigned long long* stats;
   double dt;

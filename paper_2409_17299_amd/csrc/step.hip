@@ -268,6 +268,17 @@ __device__ __forceinline__ void load_lane(const StepArgs<T>& a, const SrcTable* 
   }
 }
 
+// Waits for the loads of a lane's state and fields here, where they were
+// issued.  In a loop whose trips seldom load, the wait would otherwise stand at
+// the first use, on every trip's path, and there it also waits for the trip
+// before's log stores: loads and stores share one counter.
+template <typename T>
+__device__ __forceinline__ void await_lane(const Lane<T>& L) {
+  asm volatile("" ::"v"(L.p[0]), "v"(L.p[1]), "v"(L.p[2]), "v"(L.tau), "v"(L.id), "v"(L.w), "v"(L.root), "v"(L.t));
+  asm volatile("" ::"v"(L.x[0]), "v"(L.x[1]), "v"(L.x[2]), "v"(L.E[0]), "v"(L.E[1]), "v"(L.E[2]), "v"(L.B[0]),
+               "v"(L.B[1]), "v"(L.B[2]));
+}
+
 // What a lane stores: a child record, or its particle's final state (momentum
 // when it changed, position, optical depth; for records also the event count
 // and alive flag when asked) and, in the count kernel, the event count;
@@ -643,78 +654,99 @@ __device__ __forceinline__ LdsTables stage_tables(const StepArgs<T>& a, float* l
 
 // ------------------------------------------------------------------ work distribution
 // Lepton kernels: lanes whose particle has finished take the next one from a
-// queue held by their wave; the wave refills that queue in chunks from a
-// counter.  The particles of the launch are split into kQueueParts contiguous
-// ranges, each with its own counter on its own cache line.  A wave starts on
-// the range of its XCD (work-groups are dealt to the eight XCDs in turn) and
-// moves on to the following ranges once that one is used up.  Device-scope
+// queue held by their wave.  What it hands out is, first, pieces of the wave's
+// own (WqPlan in step.h: dealt in turn, so that a part of the ensemble with many
+// events is spread over all waves) and, in launches with more than kOwnMax
+// particles per wave, then chunks from counters that even out the rest: the
+// particles past the waves' own are split into kQueueParts contiguous ranges,
+// each with its own counter on its own cache line.  A wave starts on the range
+// of its XCD (work-groups are dealt to the eight XCDs in turn) and moves on to
+// the next range with particles left once that one is used up.  Device-scope
 // atomics that every wave of the chip sends to one address serialise at the
-// memory side; eight lines and chunks of about remaining / (2 waves of the
-// range), between kChunkMin and kChunkMax, keep that cost small, and the
-// chunks shrink towards the end so the tail stays balanced.
+// memory side; eight lines, chunks of about remaining / (2 waves of the range),
+// between kChunkMin and kChunkMax, and a look at the counters before an atomic
+// keep that cost small, and the chunks shrink towards the end so the tail stays
+// balanced.  A trip to a counter takes as long as an event or two of the whole
+// wave, which is why launches of few particles have none.
 struct WaveQueue {
-  uint64_t next, end;  // wave-uniform
-  uint32_t part, tried;
+  uint32_t next, end;  // wave-uniform
+  uint32_t own;        // pieces of its own the wave has still to start
+  uint32_t at;         // start of the next of them
+  uint32_t part;
   bool done;
 };
 
-__device__ __forceinline__ void wq_init(WaveQueue& q) {
+// wave: the wave's index in the launch (>= p.waves: it gets no work)
+__device__ __forceinline__ void wq_init(WaveQueue& q, const WqPlan& p, uint32_t wave) {
   q.next = q.end = 0;
+  q.own = wave < p.waves ? p.pieces : 0;
+  q.at = wave * p.piece;
   q.part = blockIdx.x % kQueueParts;
-  q.tried = 0;
-  q.done = false;
+  q.done = wave >= p.waves;
 }
 
-// Returns the item index of this lane (>= n: none) for lanes with need set.
+// Returns the item index of this lane (kNoItem: none) for lanes with need set.
 // ctr: kQueueParts counters, kQueueStride words apart, zero at launch.
 // kOneChunk: serve the lanes from one contiguous range only (lanes left over
 // wait for the next call), so that the lanes served get consecutive items in
 // lane order -- what the event log's records assume.
+constexpr uint32_t kNoItem = 0xFFFFFFFFu;
 template <bool kOneChunk = false>
-__device__ __forceinline__ uint64_t wq_take(WaveQueue& q, bool need, uint64_t n, unsigned long long* ctr,
-                                            uint32_t waves) {
+__device__ __forceinline__ uint32_t wq_take(WaveQueue& q, const WqPlan& p, bool need, unsigned long long* ctr) {
   uint64_t m = __ballot(need);
-  uint64_t got = ~0ull;
-  const uint64_t waves_part = waves / kQueueParts > 0 ? waves / kQueueParts : 1;
+  uint32_t got = kNoItem;
   while (m && !q.done) {
-    const uint64_t avail = q.end - q.next;
+    const uint32_t avail = q.end - q.next;
     if (avail == 0) {
-      const uint64_t lo = n * q.part / kQueueParts, hi = n * (q.part + 1) / kQueueParts, len = hi - lo;
-      unsigned long long* c = ctr + (size_t)q.part * kQueueStride;
-      uint64_t base = 0;
-      uint64_t chunk = kChunkMin;
-      if (lane_id() == 0) {
-        const uint64_t seen = __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const uint64_t rem = seen < len ? len - seen : 0;
-        chunk = rem / (2ull * waves_part);
-        chunk = chunk < kChunkMin ? kChunkMin : (chunk > kChunkMax ? kChunkMax : chunk);
-        base = seen < len ? atomicAdd(c, (unsigned long long)chunk) : len;
-      }
-      base = readlane64(base, 0);
-      chunk = readlane64(chunk, 0);
-      if (base >= len) {  // this range is used up: go on to the next one
-        if (++q.tried == kQueueParts) {
-          q.done = true;
-          break;
+      if (q.own) {
+        --q.own;
+        if (q.at < p.n) {
+          q.next = q.at;
+          q.end = q.at + p.piece < p.n ? q.at + p.piece : p.n;
+          q.at += p.waves * p.piece;
+        } else {
+          q.own = 0;
         }
-        q.part = (q.part + 1) % kQueueParts;
         continue;
       }
-      q.next = lo + base;
-      q.end = base + chunk < len ? lo + base + chunk : hi;
+      if (p.rest == 0) {
+        q.done = true;
+        break;
+      }
+      // the counters, this wave's range first
+      uint64_t v = ~0ull;
+      uint32_t len = 0, lo = 0;
+      if (lane_id() < kQueueParts) {
+        const uint32_t r = (q.part + lane_id()) % kQueueParts;
+        v = __hip_atomic_load(ctr + (size_t)r * kQueueStride, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        lo = (uint32_t)((uint64_t)p.rest * r / kQueueParts);
+        len = (uint32_t)((uint64_t)p.rest * (r + 1) / kQueueParts) - lo;
+      }
+      const uint64_t left = __ballot(v < len);
+      if (!left) {
+        q.done = true;
+        break;
+      }
+      const int at = __builtin_ctzll(left);
+      q.part = (q.part + at) % kQueueParts;
+      len = (uint32_t)__builtin_amdgcn_readlane((int)len, at);
+      lo = p.n - p.rest + (uint32_t)__builtin_amdgcn_readlane((int)lo, at);
+      uint32_t chunk = (len - (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, at)) / p.chunk_div;
+      chunk = chunk < kChunkMin ? kChunkMin : (chunk > kChunkMax ? kChunkMax : chunk);
+      uint64_t base = 0;
+      if (lane_id() == 0) base = atomicAdd(ctr + (size_t)q.part * kQueueStride, (unsigned long long)chunk);
+      base = readlane64(base, 0);
+      if (base >= len) continue;  // others took the rest in between
+      q.next = lo + (uint32_t)base;
+      q.end = lo + ((uint32_t)base + chunk < len ? (uint32_t)base + chunk : len);
       continue;
     }
     const uint32_t cnt = (uint32_t)__popcll(m);
-    const uint32_t take = (uint64_t)cnt < avail ? cnt : (uint32_t)avail;
+    const uint32_t take = cnt < avail ? cnt : avail;
     const uint32_t r = mbcnt(m);
-    if (((m >> lane_id()) & 1ull) && r < take) got = q.next + r;
-    // lanes served drop out of the mask
-    uint64_t served = 0;
-    {
-      const uint64_t mine = (((m >> lane_id()) & 1ull) && r < take) ? 1ull : 0ull;
-      served = __ballot(mine != 0);
-    }
-    m &= ~served;
+    const bool mine = ((m >> lane_id()) & 1ull) && r < take;
+    if (mine) got = q.next + r;
+    m &= ~__ballot(mine);  // lanes served drop out of the mask
     q.next += take;
     if constexpr (kOneChunk) break;
   }
@@ -833,11 +865,11 @@ template <typename T, bool kMain, bool kLog>
 __global__ void __launch_bounds__(kStepThreads, sizeof(T) == 4 ? kStepWavesPerSimd : 1) k_count_lepton(StepArgs<T> a) {
   extern __shared__ float lds[];
   const LdsTables lt = stage_tables<T, false>(a, lds);
-  const uint64_t n = (uint64_t)a.n;
-  const uint32_t waves = gridDim.x * (kStepThreads / 64);
   const uint32_t wave = blockIdx.x * (kStepThreads / 64) + (threadIdx.x >> 6);
+  // the wave's index among those that get work (the first a.block_waves of each block)
+  const uint32_t in_block = threadIdx.x >> 6, bw = (uint32_t)a.block_waves;
   WaveQueue wq;
-  wq_init(wq);
+  wq_init(wq, a.wq, in_block < bw ? blockIdx.x * bw + in_block : a.wq.waves);
   Lane<T> L;
   Outbox<T> O;
   O.what = 0;
@@ -848,11 +880,12 @@ __global__ void __launch_bounds__(kStepThreads, sizeof(T) == 4 ? kStepWavesPerSi
   int32_t local_max = 0;
   bool capped = false;
   while (true) {
-    const uint64_t k = wq_take<kLog>(wq, !have, n, a.queue, waves);
+    const uint32_t k = wq_take<kLog>(wq, a.wq, !have, a.queue);
     bool fresh = false;
-    if (!have && k < n) {
+    if (!have && k != kNoItem) {
       load_state<T, kMain>(a, lt.src, (int64_t)k, L);
       if (!kMain) load_fields<T>(lt.src, L.root, L.E, L.B);
+      await_lane<T>(L);
       q = a.species + L.part == 0 ? T(-1) : T(1);
       have = true;
       fresh = true;
@@ -1210,10 +1243,9 @@ __global__ void __launch_bounds__(kStage ? kWriteThreads : kStepThreads) k_write
                                          a.tab.cdf[0].rows32 * a.tab.cdf[0].cols32);
     wave_slots = reinterpret_cast<uint4*>(reinterpret_cast<char*>(lds) + off) + (threadIdx.x & ~63u) * kLineSlot;
   }
-  const uint64_t n = (uint64_t)*a.list_len;
-  const uint32_t waves = gridDim.x * (kThreads / 64);
+  const WqPlan plan = wq_plan((uint32_t)*a.list_len, gridDim.x * (kThreads / 64));
   WaveQueue wq;
-  wq_init(wq);
+  wq_init(wq, plan, blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6));
   Lane<T> L;
   Outbox<T> O;
   O.what = 0;
@@ -1223,12 +1255,14 @@ __global__ void __launch_bounds__(kStage ? kWriteThreads : kStepThreads) k_write
   int64_t obase = 0;
   bool have = false;
   while (true) {
-    const uint64_t e = wq_take(wq, !have, n, a.queue + kQueueWords, waves);
-    if (!have && e < n) {
+    const uint32_t e = wq_take(wq, plan, !have, a.queue + kQueueWords);
+    if (!have && e != kNoItem) {
       const int64_t k = a.list[e];
       load_state<T, kMain>(a, lt.src, k, L);
       if (!kMain) load_fields<T>(lt.src, L.root, L.E, L.B);
       obase = a.offsets[e];
+      await_lane<T>(L);
+      asm volatile("" ::"v"(obase));
       q = a.species + L.part == 0 ? T(-1) : T(1);
       have = true;
     }
