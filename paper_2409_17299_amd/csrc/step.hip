@@ -1352,23 +1352,21 @@ __device__ __forceinline__ void replay_event(const StepArgs<T>& a, Lane<T>& L, T
 // child offset plus the event index, and a lane whose particle finished moves
 // it to the end of the step and stores its final state with the logged
 // optical depth.  No tables are needed, so LDS holds only the source table
-// and (FP32) a whole 128-byte line per lane for the child records, written
-// out by eight lanes per line.
+// and a whole 128-byte line per lane for the child records, written out by
+// eight lanes per line.  Large FP32 launches only (see k_replay_events).
 constexpr int kReplayLine = 8;
-template <typename T, bool kMain, bool kStage, bool kPush, bool kPos>
-__global__ void __launch_bounds__(kStepThreads, sizeof(T) == 4 ? kStepWavesPerSimd : 1) k_replay_lepton(StepArgs<T> a) {
+template <typename T, bool kMain, bool kPush, bool kPos>
+__global__ void __launch_bounds__(kStepThreads, kStepWavesPerSimd) k_replay_lepton(StepArgs<T> a) {
   if (!a.log_on || a.log_ctl[kLogOverflow]) return;  // the direct write kernel does the writes
   if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(&a.stats[kStatReplays], 1ull);
   extern __shared__ float lds[];
-  __shared__ uint8_t owners[kStage ? kStepThreads / 64 : 1][64];
+  __shared__ uint8_t owners[kStepThreads / 64][64];
   SrcTable* src = reinterpret_cast<SrcTable*>(lds);
   stage_sources<T>(a, src);
   __syncthreads();
   constexpr int kSlot = kReplayLine + 1;
-  uint4* wave_slots = nullptr;
-  if constexpr (kStage)
-    wave_slots = reinterpret_cast<uint4*>(reinterpret_cast<char*>(lds) + sizeof(SrcTable)) +
-                 (threadIdx.x & ~63u) * kSlot;
+  uint4* wave_slots = reinterpret_cast<uint4*>(reinterpret_cast<char*>(lds) + sizeof(SrcTable)) +
+                      (threadIdx.x & ~63u) * kSlot;
   const uint32_t wave = blockIdx.x * (kStepThreads / 64) + (threadIdx.x >> 6);
   const uint64_t head = a.log_head[wave];
   if (head == 0) return;
@@ -1424,14 +1422,7 @@ __global__ void __launch_bounds__(kStepThreads, sizeof(T) == 4 ? kStepWavesPerSi
       have = true;
     }
     if (ev) {
-      T z, h;
-      if constexpr (sizeof(T) == 4) {
-        z = __builtin_bit_cast(float, sl.x);
-        h = __builtin_bit_cast(float, sl.y);
-      } else {
-        z = __builtin_bit_cast(double, join64(sl.x, sl.y));
-        h = __builtin_bit_cast(double, join64(sl.z, sl.w));
-      }
+      const T z = __builtin_bit_cast(float, sl.x), h = __builtin_bit_cast(float, sl.y);
       replay_event<T, kPush, kPos>(a, L, q, z, h, obase, O);
     } else if (fin) {
       const double tf = __builtin_bit_cast(double, join64(sl.x, sl.y));
@@ -1442,26 +1433,324 @@ __global__ void __launch_bounds__(kStepThreads, sizeof(T) == 4 ? kStepWavesPerSi
       L.tau = tf;
       stage_final<T>(a, L, true, false, true, O);
     }
-    if constexpr (kStage) {
-      if (O.what & kOutChild) {
-        stage_child<kReplayLine, T>(wave_slots + lane * kSlot, cl, a.out_rec[0], O.at, O.r);
-        if constexpr (kPos) {
-          T* qp = a.out_pos[0] + 4 * O.at;
-          qp[0] = O.x[0];
-          qp[1] = O.x[1];
-          qp[2] = O.x[2];
-          qp[3] = T(0);
-        }
-        O.what &= ~kOutChild;
+    if (O.what & kOutChild) {
+      stage_child<kReplayLine, T>(wave_slots + lane * kSlot, cl, a.out_rec[0], O.at, O.r);
+      if constexpr (kPos) {
+        T* qp = a.out_pos[0] + 4 * O.at;
+        qp[0] = O.x[0];
+        qp[1] = O.x[1];
+        qp[2] = O.x[2];
+        qp[3] = T(0);
       }
+      O.what &= ~kOutChild;
     }
     flush<T>(a, src, O);
-    if constexpr (kStage) line_flush<kReplayLine, T>(wave_slots, owners[threadIdx.x >> 6], cl, fin);
+    line_flush<kReplayLine, T>(wave_slots, owners[threadIdx.x >> 6], cl, fin);
     if (fin) have = false;
     h0 = h0_n;
     h1 = h1_n;
     sl = sl_n;
     pos += 1;
+  }
+}
+
+// The same pass for launches of few particles, with the events of a log in
+// parallel.  Only the momentum, the time and the position run from one event of
+// a particle to the next, a dozen instructions; the rest of an event (the
+// fraction, two Philox draws, the child's optical depth, the record) depends on
+// that event alone.  In a launch with one wave per SIMD nothing hides that
+// chain, and going through all of it event by event (k_replay_lepton) takes
+// about as long as the count pass.  So one block per log takes kTrips records
+// at a time, with a tile of kTrips x 64 entries in LDS:
+//   1. all waves: the slots, the fractions of the events and the states of the
+//      particles that begin, every load of the tile in flight together;
+//   2. one wave, lane by lane as the count wave ran: momentum, time and event
+//      number of each event, and the state at the end of each particle;
+//   3. all waves, an entry per thread: child records and final states; a wave
+//      takes kTrips trips of 64 / kTrips lanes, so the children of one parent
+//      are stored next to each other.
+// Write pass of 1e3 crossed-field particles 367 -> 125 us (all rounds), of 1e5
+// electrons in a static field 130 -> 79 us.  FP32 launches with more than one
+// wave per SIMD keep k_replay_lepton: the chains hide one another, its records
+// leave in whole lines, and here three waves of a block wait for the second
+// phase and LDS holds four blocks per CU (4e6 particles: 5.5 ms there, 6.2 ms
+// here; 1e6 leptons with one event each: 40 against 56 us).  In FP64, where
+// that kernel stored its records piece by piece, this one is the faster at every
+// size (the step of 2e5 particles 4.78 against 4.62 ms, of 1.5e6 19.06 against
+// 18.21).
+constexpr int kReplayThreads = 256, kReplayWaves = kReplayThreads / 64;
+constexpr uint32_t kEntryEvent = 0x40000000u, kEntryFinal = 0x80000000u;
+
+// Offsets of the tile's arrays (in entries' worth of T, then 32-bit words).
+template <typename T, bool kMain, bool kPush, bool kPos>
+struct ReplayTile {
+  // entries are 32 bytes (FP32) and up; more trips at once than this leave too few blocks per CU
+  static constexpr int kTrips = sizeof(T) == 4 && !kPush && !kPos ? 16 : 8;
+  // phase 3's waves take kMapTrips trips of 64 / kMapTrips lanes; the pitch puts their entries in different banks
+  static constexpr int kMapTrips = kTrips, kMapLanes = 64 / kMapTrips, kPitch = 64 + kMapLanes;
+  static constexpr int kN = kTrips * kPitch;
+  static constexpr int kArrays = 6 + (kMain ? 0 : 1) + (kPush ? 6 : 0) + (kPos ? 3 : 0);
+  static constexpr size_t kBytes = (size_t)kN * (kArrays * sizeof(T) + 8);
+  T *d, *omd, *h, *p, *t0, *f, *x;  // p, f, x: kN apart per component
+  uint32_t *k, *j;
+  __device__ explicit ReplayTile(char* at) {
+    T* v = reinterpret_cast<T*>(at);
+    d = v;
+    omd = v + kN;
+    h = v + 2 * kN;
+    p = v + 3 * kN;
+    t0 = v + 6 * kN;
+    f = t0 + (kMain ? 0 : kN);
+    x = f + (kPush ? 6 * kN : 0);
+    k = reinterpret_cast<uint32_t*>(v + kArrays * kN);
+    j = k + kN;
+  }
+};
+
+template <typename T, bool kMain, bool kPush, bool kPos>
+__global__ void __launch_bounds__(kReplayThreads, sizeof(T) == 4 ? 4 : 2) k_replay_events(StepArgs<T> a) {
+  if (!a.log_on || a.log_ctl[kLogOverflow]) return;  // the direct write kernel does the writes
+  if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(&a.stats[kStatReplays], 1ull);
+  const uint64_t head = a.log_head[blockIdx.x];
+  if (head == 0) return;
+  using Tile = ReplayTile<T, kMain, kPush, kPos>;
+  constexpr int kTrips = Tile::kTrips, kN = Tile::kN, kPerWave = kTrips / kReplayWaves;
+  extern __shared__ float lds[];
+  SrcTable* src = reinterpret_cast<SrcTable*>(lds);
+  stage_sources<T>(a, src);
+  const Tile tile(reinterpret_cast<char*>(lds) + sizeof(SrcTable));
+  __syncthreads();
+  constexpr uint32_t S = log_slot_bytes<T>();
+  constexpr uint64_t R = log_record_bytes(S);
+  constexpr int kPer = (int)log_records_per_block(S);
+  const T dtT = (T)a.dt;
+  const int lane = lane_id(), wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  uint64_t blk = head - 1;
+  int pos = 0;
+  // wave 0: the particle each lane of the count wave holds
+  Lane<T> L;
+  T q = T(-1);
+  uint32_t k = 0;
+  bool have = false;
+  while (true) {
+    // lane t: the header of record pos + t; records end at the first marker
+    // (every block of the log has one, its last position at the latest)
+    const int room = kPer - pos < kTrips ? kPer - pos : kTrips;
+    const char* rec0 = a.log_pool + blk + (uint64_t)pos * R;
+    uint4 h0 = make_uint4(0, 0, 0, 0), h1 = h0;
+    if (lane < room) {
+      const uint4* r = reinterpret_cast<const uint4*>(rec0 + (uint64_t)lane * R);
+      h0 = r[0];
+      h1 = r[1];
+    }
+    const uint64_t marks = __ballot(lane < room && join64(h1.z, h1.w) != kLogRecord);
+    const int nrec = marks ? __builtin_ctzll(marks) : room;
+    const uint64_t tag = readlane64(join64(h1.z, h1.w), nrec & 63), next = readlane64(join64(h1.x, h1.y), nrec & 63);
+    auto trip = [&](int t, uint64_t& m_fresh, uint64_t& m_ev) {
+      m_fresh = readlane64(join64(h0.x, h0.y), t);
+      m_ev = readlane64(join64(h0.z, h0.w), t);
+    };
+    if (nrec) {
+      // phase 1
+      LogSlot<T> sl[kPerWave];
+      bool fr[kPerWave];
+      T p1[kPerWave][3], x1[kPerWave][3], f1[kPerWave][6], t1[kPerWave];
+      uint32_t k1[kPerWave];
+#pragma unroll
+      for (int i = 0; i < kPerWave; ++i) {
+        const int t = wv + kReplayWaves * i < nrec ? wv + kReplayWaves * i : nrec - 1;
+        sl[i] = *reinterpret_cast<const LogSlot<T>*>(rec0 + (uint64_t)t * R + kLogHeader + (uint64_t)S * lane);
+      }
+#pragma unroll
+      for (int i = 0; i < kPerWave; ++i) {
+        const int t = wv + kReplayWaves * i;
+        fr[i] = false;
+        if (t >= nrec) continue;
+        uint64_t m_fresh, m_ev;
+        trip(t, m_fresh, m_ev);
+        k1[i] = (uint32_t)(readlane64(join64(h1.x, h1.y), t) + mbcnt(m_fresh));  // log_fresh_index
+        fr[i] = (m_fresh & m_ev & (1ull << lane)) != 0;  // a new particle with an event
+        if (!fr[i]) continue;
+        Lane<T> N;
+        load_state<T, kMain, kPush>(a, src, k1[i], N);
+        if (!kMain && kPush) load_fields<T>(src, N.root, N.E, N.B);
+        for (int c = 0; c < 3; ++c) {
+          p1[i][c] = N.p[c];
+          if (kPos) x1[i][c] = N.x[c];
+          if (kPush) {
+            f1[i][c] = N.E[c];
+            f1[i][3 + c] = N.B[c];
+          }
+        }
+        t1[i] = N.t;
+      }
+#pragma unroll
+      for (int i = 0; i < kPerWave; ++i) {
+        const int t = wv + kReplayWaves * i, e = t * Tile::kPitch + lane;
+        if (t >= nrec) continue;
+        uint64_t m_fresh, m_ev;
+        trip(t, m_fresh, m_ev);
+        T z, h;
+        if constexpr (sizeof(T) == 4) {
+          z = __builtin_bit_cast(float, sl[i].x);
+          h = __builtin_bit_cast(float, sl[i].y);
+        } else {
+          z = __builtin_bit_cast(double, join64(sl[i].x, sl[i].y));
+          h = __builtin_bit_cast(double, join64(sl[i].z, sl[i].w));
+        }
+        T d = z, omd = T(0);  // a finished particle's slot: its optical depth, bits kept as they are
+        if ((m_ev >> lane) & 1ull) sigmoid_of<T>(z, d, omd);
+        tile.d[e] = d;
+        tile.omd[e] = omd;
+        tile.h[e] = h;
+        if (fr[i]) {
+          for (int c = 0; c < 3; ++c) {
+            tile.p[c * kN + e] = p1[i][c];
+            if (kPos) tile.x[c * kN + e] = x1[i][c];
+            if (kPush) {
+              tile.f[c * kN + e] = f1[i][c];
+              tile.f[(3 + c) * kN + e] = f1[i][3 + c];
+            }
+          }
+          if (!kMain) tile.t0[e] = t1[i];
+          tile.k[e] = k1[i];
+        }
+      }
+      __syncthreads();
+      // phase 2
+      if (wv == 0) {
+        for (int t = 0; t < nrec; ++t) {
+          uint64_t m_fresh, m_ev;
+          trip(t, m_fresh, m_ev);
+          const int e = t * Tile::kPitch + lane;
+          uint32_t what = 0;
+          if ((m_ev >> lane) & 1ull) {
+            const T omd = tile.omd[e], h = tile.h[e];
+            if ((m_fresh >> lane) & 1ull) {
+              for (int c = 0; c < 3; ++c) {
+                L.p[c] = tile.p[c * kN + e];
+                if (kPos) L.x[c] = tile.x[c * kN + e];
+                if (kPush) {
+                  L.E[c] = tile.f[c * kN + e];
+                  L.B[c] = tile.f[(3 + c) * kN + e];
+                }
+              }
+              L.t = kMain ? T(0) : tile.t0[e];
+              L.j = 0;
+              k = tile.k[e];
+              q = a.species + ((int64_t)k >= a.n0 ? 1 : 0) == 0 ? T(-1) : T(1);
+              have = true;
+            }
+            advance_lepton_ct<T, kPush, kPos>(L, q, h);
+            L.t += h;
+            tile.h[e] = L.t;
+            what = (uint32_t)L.j | kEntryEvent;
+            for (int c = 0; c < 3; ++c) tile.p[c * kN + e] = L.p[c];
+            L.p[0] *= omd;
+            L.p[1] *= omd;
+            L.p[2] *= omd;
+            ++L.j;
+          } else if (have) {
+            if (L.t < dtT) advance_lepton_ct<T, kPush, kPos>(L, q, dtT - L.t);  // the count pass's last trip
+            what = (uint32_t)L.j | kEntryFinal;
+            for (int c = 0; c < 3; ++c) tile.p[c * kN + e] = L.p[c];
+            have = false;
+          }
+          if (what) {
+            tile.k[e] = k;
+            if (kPos)
+              for (int c = 0; c < 3; ++c) tile.x[c * kN + e] = L.x[c];
+          }
+          tile.j[e] = what;
+        }
+      }
+      __syncthreads();
+      // phase 3
+#pragma unroll
+      for (int i = 0; i < kPerWave; ++i) {
+        const int b = wv + kReplayWaves * i;
+        const int t = lane % Tile::kMapTrips, e = t * Tile::kPitch + b * Tile::kMapLanes + lane / Tile::kMapTrips;
+        const uint32_t what = t < nrec ? tile.j[e] : 0u;
+        if (!what) continue;
+        const uint32_t ke = tile.k[e];
+        const int part = (int64_t)ke >= a.n0 ? 1 : 0;
+        const uint64_t* w = src->part[part];
+        const int64_t is = (int64_t)w[kBegin] + (part ? (int64_t)ke - a.n0 : (int64_t)ke);
+        Rec<T> r;
+        r.px = tile.p[e];
+        r.py = tile.p[kN + e];
+        r.pz = tile.p[2 * kN + e];
+        if constexpr (kMain) {
+          r.id = gptr<const uint64_t>(w[kId])[is];
+          r.w = gptr<const float>(w[kW])[is];
+          r.root = ((uint32_t)(a.species + part) << 30) | (uint32_t)is;
+          r.tb = T(0);
+        } else {
+          Rec<T> s;
+          rec_load<T>(gptr<const Rec<T>>(w[kRec]), is, s);
+          r.id = s.id;
+          r.w = s.w;
+          r.root = s.root;
+          r.tb = s.tb;
+        }
+        const uint32_t j = what & 0x3FFFFFFFu;
+        if (what & kEntryEvent) {  // the photon: k = delta p, born here
+          const int64_t o = a.offsets_k[ke] + j;
+          if (o >= a.out_cap) continue;
+          const T d = tile.d[e];
+          const uint32_t u = draw(a.seed, r.id, a.step, j).z;
+          const uint4 v = draw(a.seed, r.id, a.step, j | 0x80000000u);
+          r.px = d * r.px;
+          r.py = d * r.py;
+          r.pz = d * r.pz;
+          r.tb = tile.h[e];
+          r.tau = exp_depth_t<T>(u);
+          r.id = (uint64_t)v.x | ((uint64_t)v.y << 32);
+          r.nev = 0;
+          r.alive = 1u;
+          rec_store<T>(a.out_rec[0], o, r);
+          if constexpr (kPos) {
+            T* qp = a.out_pos[0] + 4 * o;
+            for (int c = 0; c < 3; ++c) qp[c] = tile.x[c * kN + e];
+            qp[3] = T(0);
+          }
+        } else {  // the particle's final state
+          if constexpr (sizeof(T) == 4)
+            r.tau = __builtin_bit_cast(double, join64(fbits(tile.d[e]), fbits(tile.h[e])));
+          else
+            r.tau = tile.d[e];
+          r.nev = (int32_t)j;
+          r.alive = 1u;
+          if constexpr (kMain) {
+            gptr<T>(w[kPx])[is] = r.px;
+            gptr<T>(w[kPy])[is] = r.py;
+            gptr<T>(w[kPz])[is] = r.pz;
+            gptr<double>(w[kTau])[is] = r.tau;
+            if constexpr (kPos) {
+              gptr<T>(w[kX])[is] = tile.x[e];
+              gptr<T>(w[kY])[is] = tile.x[kN + e];
+              gptr<T>(w[kZ])[is] = tile.x[2 * kN + e];
+            }
+          } else {
+            using C = RecChunks<T>;
+            rec_store_part<T>(gptr<Rec<T>>(w[kRec]), is, r, 0, a.write_nev ? C::kCount : C::kTail);
+            if constexpr (kPos) {
+              T* qp = gptr<T>(w[SrcWord::kPos]) + 4 * is;  // (kPos alone is the template's flag)
+              for (int c = 0; c < 3; ++c) qp[c] = tile.x[c * kN + e];
+            }
+          }
+        }
+      }
+      __syncthreads();  // the tile is free again
+    }
+    if (!marks) {
+      pos += nrec;
+    } else if (tag == kLogJump) {  // the block the log goes on in
+      blk = next;
+      pos = 0;
+    } else {
+      break;
+    }
   }
 }
 
@@ -1975,18 +2264,25 @@ hipError_t launch_write(const StepArgs<T>& a, int grid, size_t lds, hipStream_t 
   if (a.from_main) return launch_step_kernel(&k_write_lepton<T, true, false>, a, grid, lds, st);
   return launch_step_kernel(&k_write_lepton<T, false, false>, a, grid, lds, st);
 }
-// The replay runs the count launch's grid (512-thread blocks); FP32 stages its
-// child records in LDS half lines.
+// The replay by lanes runs the count launch's grid, the replay by events one
+// block per wave of it.  By events: FP64, and FP32 launches with one wave per
+// SIMD (measured beside k_replay_events).
+template <typename T, bool kMain, bool kPush, bool kPos>
+hipError_t launch_replay_as(const StepArgs<T>& a, int grid, hipStream_t st) {
+  if constexpr (sizeof(T) == 4) {
+    if (a.block_waves == kStepThreads / 64)
+      return launch_step_kernel(&k_replay_lepton<T, kMain, kPush, kPos>, a, grid,
+                                sizeof(SrcTable) + (size_t)kStepThreads * (kReplayLine + 1) * 16, st);
+  }
+  return launch_step_kernel(&k_replay_events<T, kMain, kPush, kPos>, a, grid * (kStepThreads / 64),
+                            sizeof(SrcTable) + ReplayTile<T, kMain, kPush, kPos>::kBytes, st, kReplayThreads);
+}
 template <typename T, bool kMain>
 hipError_t launch_replay_main(const StepArgs<T>& a, int grid, hipStream_t st) {
-  constexpr bool kStage = sizeof(T) == 4;
-  const size_t lds = sizeof(SrcTable) + (kStage ? (size_t)kStepThreads * (kReplayLine + 1) * 16 : 0);
-  if (a.push) {
-    if (a.positions) return launch_step_kernel(&k_replay_lepton<T, kMain, kStage, true, true>, a, grid, lds, st);
-    return launch_step_kernel(&k_replay_lepton<T, kMain, kStage, true, false>, a, grid, lds, st);
-  }
-  if (a.positions) return launch_step_kernel(&k_replay_lepton<T, kMain, kStage, false, true>, a, grid, lds, st);
-  return launch_step_kernel(&k_replay_lepton<T, kMain, kStage, false, false>, a, grid, lds, st);
+  if (a.push) return a.positions ? launch_replay_as<T, kMain, true, true>(a, grid, st)
+                                 : launch_replay_as<T, kMain, true, false>(a, grid, st);
+  return a.positions ? launch_replay_as<T, kMain, false, true>(a, grid, st)
+                     : launch_replay_as<T, kMain, false, false>(a, grid, st);
 }
 template <typename T>
 hipError_t launch_replay(const StepArgs<T>& a, int grid, hipStream_t st) {
