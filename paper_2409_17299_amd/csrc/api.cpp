@@ -730,7 +730,8 @@ qed_status step_impl(const qed_tables* tab, const qed_step_cfg* cfg, qed_ensembl
   local.n_new[1] = cur[1];
   local.n_new[2] = cur[0];
   local.n_rounds = rounds;
-  local.max_events = (int64_t)dev_stats[kStatMaxEvents];
+  // the kernels keep the leptons' largest count; a photon has at most one event
+  local.max_events = std::max<int64_t>((int64_t)dev_stats[kStatMaxEvents], dev_stats[kStatEventParticles + 1] ? 1 : 0);
   local.required_capacity[0] = cur[1];
   local.required_capacity[1] = cur[1];
   local.required_capacity[2] = cur[0];

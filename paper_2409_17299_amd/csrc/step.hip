@@ -805,7 +805,7 @@ __device__ __forceinline__ void log_header(char* at, uint64_t w0, uint64_t w1, u
 // particle, which had events, finished; fresh, it took a new particle at the
 // start of the trip (its launch index in L.k).
 template <typename T>
-__device__ __forceinline__ void log_trip(const StepArgs<T>& a, LogWriter& w, uint32_t wave, bool ev,
+__device__ __forceinline__ void log_trip(const StepArgs<T>& a, LogWriter& w, uint32_t wave, uint32_t active, bool ev,
                                          bool fin_with_events, bool fresh, const Lane<T>& L) {
   constexpr uint32_t S = log_slot_bytes<T>();
   constexpr uint64_t R = log_record_bytes(S);
@@ -817,9 +817,11 @@ __device__ __forceinline__ void log_trip(const StepArgs<T>& a, LogWriter& w, uin
   if (w.state == 2) return;
   const int lane = lane_id();
   if (w.state == 0 || w.pos + 1 >= kPer) {  // the block's last position is kept for a marker
-    uint32_t b = 0;
-    if (lane == 0) b = (uint32_t)(atomicAdd(a.log_ctl + kLogUsed, 1ull));
-    b = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
+    uint32_t b = active;  // its first block is the wave's own; further ones are handed out after all of those
+    if (w.state) {
+      if (lane == 0) b = a.wq.waves + (uint32_t)(atomicAdd(a.log_ctl + kLogUsed, 1ull));
+      b = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
+    }
     const uint64_t blk = (uint64_t)b * kLogBlock;
     if (blk + kLogBlock > a.log_cap) {
       if (lane == 0) atomicOr(a.log_ctl + kLogOverflow, 1ull);
@@ -844,17 +846,32 @@ __device__ __forceinline__ void log_trip(const StepArgs<T>& a, LogWriter& w, uin
   w.pos += 1;
 }
 
+// Closes the wave's log; returns the blocks of the pool it takes.
 template <typename T>
-__device__ __forceinline__ void log_close(const StepArgs<T>& a, const LogWriter& w, uint32_t wave) {
+__device__ __forceinline__ uint32_t log_close(const StepArgs<T>& a, const LogWriter& w, uint32_t wave) {
   constexpr uint64_t R = log_record_bytes(log_slot_bytes<T>());
   constexpr uint64_t kPer = log_records_per_block(log_slot_bytes<T>());
-  if (lane_id() != 0) return;
-  if (w.state == 0) a.log_head[wave] = 0;
-  else if (w.state == 1) log_header(a.log_pool + (uint64_t)w.blk * kLogBlock + (uint64_t)w.pos * R, 0, 0, 0, kLogEnd);
+  if (lane_id() == 0) {
+    if (w.state == 0) a.log_head[wave] = 0;
+    else if (w.state == 1)
+      log_header(a.log_pool + (uint64_t)w.blk * kLogBlock + (uint64_t)w.pos * R, 0, 0, 0, kLogEnd);
+  }
   // the blocks this wave's records take (each block keeps its last position
-  // for a marker), plus one for the end marker
-  if (w.recs) atomicAdd(a.log_ctl + kLogNeed, (unsigned long long)(w.recs / (kPer - 1) + 2) * kLogBlock);
+  // for a marker), plus one for the end marker; without records its first
+  // block is still its own
+  return w.recs ? w.recs / (uint32_t)(kPer - 1) + 2 : 1;
 }
+
+// What the waves of a block add to the launch's words when they end, collected
+// in LDS so that the last of them does it with one atomic per word.  Device
+// atomics to one address take about 12 ns each, one after another: two from
+// each of a launch's 4096 waves were 100 us in which nothing else was left
+// to do (and as much again in the photon kernels, where every wave raised the
+// largest event count to 1; the host takes that from the number of photons
+// with events).
+struct BlockTotals {
+  uint32_t ended, max_events, log_blocks, capped;
+};
 
 // ------------------------------------------------------------------ count kernels
 // Leptons: event counts vary from 0 to hundreds, so lanes refill.
@@ -864,12 +881,15 @@ __device__ __forceinline__ void log_close(const StepArgs<T>& a, const LogWriter&
 template <typename T, bool kMain, bool kLog>
 __global__ void __launch_bounds__(kStepThreads, sizeof(T) == 4 ? kStepWavesPerSimd : 1) k_count_lepton(StepArgs<T> a) {
   extern __shared__ float lds[];
-  const LdsTables lt = stage_tables<T, false>(a, lds);
+  __shared__ BlockTotals totals;
+  if (threadIdx.x == 0) totals = BlockTotals{0, 0, 0, 0};
+  const LdsTables lt = stage_tables<T, false>(a, lds);  // synchronises the block
   const uint32_t wave = blockIdx.x * (kStepThreads / 64) + (threadIdx.x >> 6);
   // the wave's index among those that get work (the first a.block_waves of each block)
   const uint32_t in_block = threadIdx.x >> 6, bw = (uint32_t)a.block_waves;
   WaveQueue wq;
-  wq_init(wq, a.wq, in_block < bw ? blockIdx.x * bw + in_block : a.wq.waves);
+  const uint32_t active = in_block < bw ? blockIdx.x * bw + in_block : a.wq.waves;
+  wq_init(wq, a.wq, active);
   Lane<T> L;
   Outbox<T> O;
   O.what = 0;
@@ -902,16 +922,33 @@ __global__ void __launch_bounds__(kStepThreads, sizeof(T) == 4 ? kStepWavesPerSi
         capped |= L.capped;
       }
     }
-    if constexpr (kLog) log_trip<T>(a, lw, wave, have && !fin, have && fin && L.j > 0, fresh, L);
+    if constexpr (kLog) log_trip<T>(a, lw, wave, active, have && !fin, have && fin && L.j > 0, fresh, L);
     if (fin) have = false;
   }
-  if constexpr (kLog) log_close<T>(a, lw, wave);
   for (int off = 32; off > 0; off >>= 1) {
     const int32_t o = __shfl_xor(local_max, off);
     local_max = o > local_max ? o : local_max;
   }
-  if (lane_id() == 0 && local_max > 0) atomicMax(&a.stats[kStatMaxEvents], (unsigned long long)local_max);
-  if (__any(capped) && lane_id() == 0) atomicOr(&a.stats[kStatCapped], 1ull);
+  const bool any_capped = __any(capped);
+  uint32_t blocks = 0;
+  if constexpr (kLog) {
+    blocks = log_close<T>(a, lw, wave);
+    if (in_block >= bw) blocks = 0;
+  }
+  if (lane_id() == 0) {
+    atomicMax(&totals.max_events, (uint32_t)local_max);
+    if (blocks) atomicAdd(&totals.log_blocks, blocks);
+    if (any_capped) atomicOr(&totals.capped, 1u);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    if (atomicAdd(&totals.ended, 1u) == kStepThreads / 64 - 1) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+      volatile BlockTotals* t = &totals;
+      const uint32_t m = t->max_events, c = t->capped, lb = t->log_blocks;
+      if (m) atomicMax(&a.stats[kStatMaxEvents], (unsigned long long)m);
+      if (c) atomicOr(&a.stats[kStatCapped], 1ull);
+      if (kLog && lb) atomicAdd(a.log_ctl + kLogNeed, (unsigned long long)lb * kLogBlock);
+    }
+  }
 }
 
 // Photons: at most one event each; one photon per thread.
@@ -919,7 +956,6 @@ template <typename T>
 __global__ void __launch_bounds__(kStepThreads, sizeof(T) == 4 ? kStepWavesPerSimd : 1) k_count_photon(StepArgs<T> a) {
   extern __shared__ float lds[];
   const LdsTables lt = stage_tables<T, true>(a, lds);
-  int32_t any_event = 0;
   for (int64_t k = (int64_t)blockIdx.x * kStepThreads + threadIdx.x; k < a.n;
        k += (int64_t)gridDim.x * kStepThreads) {
     Lane<T> L;
@@ -932,9 +968,7 @@ __global__ void __launch_bounds__(kStepThreads, sizeof(T) == 4 ? kStepWavesPerSi
     a.counts[k] = L.j;
     if (a.from_main && a.src[0].nev) a.src[0].nev[L.i] = L.j;
     if (L.j == 0) store_final<T>(a, lt.src, L, false, false);
-    any_event |= L.j;
   }
-  if (__any(any_event) && lane_id() == 0) atomicMax(&a.stats[kStatMaxEvents], 1ull);
 }
 
 // The photon count pass of an appended range with the merge folded in: tiles
@@ -971,7 +1005,6 @@ __global__ void __launch_bounds__(kStepThreads, sizeof(T) == 4 ? kStepWavesPerSi
   }
   const int lane = lane_id(), wave = threadIdx.x >> 6;
   const int64_t dst0 = *a.dst_cursor, pair0 = *a.pair_cursor;
-  int32_t any_event = 0;
   while (true) {
     __syncthreads();  // the previous tile's readers of s_tile, s_base and wsum are done
     if (threadIdx.x == 0) s_tile = (int64_t)atomicAdd(a.dst_ticket, 1ull);
@@ -990,7 +1023,6 @@ __global__ void __launch_bounds__(kStepThreads, sizeof(T) == 4 ? kStepWavesPerSi
         Lane<T> L;
         load_lane<T>(a, lt.src, k, L);
         photon_iter<T, false>(a, lt, L, 0);
-        any_event |= L.j;
         event |= (L.j != 0 ? 1u : 0u) << it;
         if (L.j == 0) {
           surv |= 1u << it;
@@ -1068,7 +1100,6 @@ __global__ void __launch_bounds__(kStepThreads, sizeof(T) == 4 ? kStepWavesPerSi
       d.alive[o] = 1;
     }
   }
-  if (__any(any_event) && lane_id() == 0) atomicMax(&a.stats[kStatMaxEvents], 1ull);
 }
 
 // ------------------------------------------------------------------ scan kernel
