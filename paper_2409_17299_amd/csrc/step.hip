@@ -990,7 +990,6 @@ template <typename T>
 __global__ void __launch_bounds__(kStepThreads, sizeof(T) == 4 ? kStepWavesPerSimd : 1)
     k_count_photon_merged(StepArgs<T> a) {
   extern __shared__ float lds[];
-  const LdsTables lt = stage_tables<T, true>(a, lds);
   __shared__ int32_t wsum[kMergedItems][kStepThreads / 64];
   __shared__ int64_t s_tile, s_base;
   int64_t n = a.n;
@@ -1003,6 +1002,9 @@ __global__ void __launch_bounds__(kStepThreads, sizeof(T) == 4 ? kStepWavesPerSi
     if (blockIdx.x == 0 && threadIdx.x == 0) *const_cast<int64_t*>(a.list_len) = 0;
     return;
   }
+  // the grid is sized for the append buffer; blocks past the range's tiles leave before they stage the tables
+  if ((int64_t)blockIdx.x >= num_tiles) return;
+  const LdsTables lt = stage_tables<T, true>(a, lds);
   const int lane = lane_id(), wave = threadIdx.x >> 6;
   const int64_t dst0 = *a.dst_cursor, pair0 = *a.pair_cursor;
   while (true) {
@@ -1788,8 +1790,9 @@ __global__ void __launch_bounds__(kReplayThreads, sizeof(T) == 4 ? 4 : 2) k_repl
 template <typename T>
 __global__ void __launch_bounds__(kStepThreads, sizeof(T) == 4 ? kStepWavesPerSimd : 1) k_write_photon(StepArgs<T> a) {
   extern __shared__ float lds[];
-  const LdsTables lt = stage_tables<T, true>(a, lds);
   const int64_t n = *a.list_len;
+  if ((int64_t)blockIdx.x * kStepThreads >= n) return;
+  const LdsTables lt = stage_tables<T, true>(a, lds);
   for (int64_t e = (int64_t)blockIdx.x * kStepThreads + threadIdx.x; e < n; e += (int64_t)gridDim.x * kStepThreads) {
     const int64_t k = a.list[e];
     Lane<T> L;
