@@ -912,35 +912,54 @@ qed_status resample_impl(qed_ensemble* ens, const qed_resample_cfg* cfg, qed_res
   qed_resample_stats stats;
   std::memset(&stats, 0, sizeof(stats));
   const double e_min2 = cfg->photon_energy_min > 0.0 ? cfg->photon_energy_min * cfg->photon_energy_min : 0.0;
-  bool solve[3] = {false, false, false};
+  LevelArgs<T> lv;
+  std::memset(&lv, 0, sizeof(lv));
+  lv.e_min2 = e_min2;
+  lv.state = dstate;
+  lv.part = S->level;
+  int passes = 0;
   for (int k = 0; k < 3; ++k) {
     const int64_t n = ens->s[k].count;
     stats.count_before[k] = stats.count_after[k] = n;
     const bool filter = k == 2 && e_min2 > 0.0;
-    solve[k] = n > 0 && (filter || cfg->target[k] > 0);
-    if (!solve[k]) continue;
-    const SpeciesView<T> v = view_of<T>(ens->s[k]);
-    const int passes = cfg->target[k] > 0 ? 1 + S->level_passes[k] : 1;
-    for (int q = 0; q < passes; ++q)
-      SFQED_HIP(launch_level_pass<T>(v, n, k == 2 ? 1 : 0, e_min2, cfg->target[k], q == 0 ? 1 : 0,
-                                     S->level + k * part_words, dstate + k, st));
+    lv.solve[k] = n > 0 && (filter || cfg->target[k] > 0);
+    if (!lv.solve[k]) continue;
+    lv.s[k] = view_of<T>(ens->s[k]);
+    lv.n[k] = n;
+    lv.target[k] = cfg->target[k];
+    passes = std::max(passes, cfg->target[k] > 0 ? 1 + S->level_passes[k] : 1);
   }
+  if (lv.solve[2] && e_min2 > 0.0) {  // a bit per photon, in the scratch of the launches' offsets
+    const qed_status rc = ensure_scratch(S, (lv.n[2] + 63) / 64);
+    if (rc != QED_OK) return rc;
+    lv.mask = reinterpret_cast<uint64_t*>(S->offsets);
+  }
+  for (int q = 0; q < passes; ++q) SFQED_HIP(launch_level_pass<T>(lv, q == 0 ? 1 : 0, st));
   LevelState ls[3];
   qed_status rb = read_back(S, ls, dstate, sizeof(ls), st);
   if (rb != QED_OK) return rb;
-  for (int k = 0; k < 3; ++k) {
-    if (!solve[k]) continue;
-    const SpeciesView<T> v = view_of<T>(ens->s[k]);
-    while (!ls[k].done && ls[k].iterations < 100) {
-      SFQED_HIP(launch_level_pass<T>(v, ens->s[k].count, k == 2 ? 1 : 0, e_min2, cfg->target[k], 0,
-                                     S->level + k * part_words, dstate + k, st));
-      if ((rb = read_back(S, &ls[k], dstate + k, sizeof(LevelState), st)) != QED_OK) return rb;
+  // solves that have not finished go on one pass at a time
+  while (true) {
+    LevelArgs<T> more = lv;
+    bool any = false;
+    for (int k = 0; k < 3; ++k) {
+      more.solve[k] = lv.solve[k] && !ls[k].done && ls[k].iterations < 100;
+      any |= more.solve[k] != 0;
     }
-    if (cfg->target[k] > 0) S->level_passes[k] = std::max(2, std::min(kLevelDevicePasses, ls[k].iterations + 1));
+    if (!any) break;
+    SFQED_HIP(launch_level_pass<T>(more, 0, st));
+    if ((rb = read_back(S, ls, dstate, sizeof(ls), st)) != QED_OK) return rb;
   }
+  for (int k = 0; k < 3; ++k)
+    if (lv.solve[k] && cfg->target[k] > 0)
+      S->level_passes[k] = std::max(2, std::min(kLevelDevicePasses, ls[k].iterations + 1));
   bool compacted[3] = {false, false, false};
+  ResampleLaunch<T> la;
+  std::memset(&la, 0, sizeof(la));
+  int64_t tiles = 0;
   for (int k = 0; k < 3; ++k) {
-    if (!solve[k]) continue;
+    la.first_block[k] = tiles;
+    if (!lv.solve[k]) continue;
     const int64_t n = ens->s[k].count;
     const bool photon = k == 2, filter = photon && e_min2 > 0.0;
     const int64_t eligible = (int64_t)ls[k].eligible;
@@ -949,22 +968,7 @@ qed_status resample_impl(qed_ensemble* ens, const qed_resample_cfg* cfg, qed_res
     stats.w_threshold[k] = wt;
     if (photon) stats.filtered = n - eligible;
     if (wt <= 0.0 && !(filter && eligible < n)) continue;  // nothing to remove
-    const int64_t tiles = (n + kMergeTile - 1) / kMergeTile;
-    if (tiles > S->tiles_cap) {
-      if (S->state_c) {
-        SFQED_HIP(hipDeviceSynchronize());
-        (void)hipFree(S->state_c);
-        (void)hipFree(S->state_f);
-      }
-      SFQED_HIP(hipMalloc(&S->state_c, sizeof(uint64_t) * tiles));
-      SFQED_HIP(hipMalloc(&S->state_f, sizeof(uint64_t) * tiles));
-      SFQED_HIP(hipMemset(S->state_c, 0, sizeof(uint64_t) * tiles));
-      SFQED_HIP(hipMemset(S->state_f, 0, sizeof(uint64_t) * tiles));
-      S->tiles_cap = tiles;
-      S->epoch = 0;
-    }
-    SFQED_HIP(hipMemsetAsync(S->ctrl, 0, sizeof(uint64_t), st));
-    ResampleArgs<T> a;
+    ResampleArgs<T>& a = la.a[k];
     a.s = view_of<T>(ens->s[k]);
     a.n = n;
     a.photon = photon ? 1 : 0;
@@ -973,17 +977,26 @@ qed_status resample_impl(qed_ensemble* ens, const qed_resample_cfg* cfg, qed_res
     a.wt = wt;
     a.seed = cfg->seed;
     a.step = cfg->step;
-    a.state = S->state_c;
-    a.epoch = next_epoch(S, st);
-    if (!a.epoch) {
+    a.ticket = reinterpret_cast<unsigned long long*>(S->ctrl + k);
+    a.num_tiles = (n + kMergeTile - 1) / kMergeTile;
+    a.out_count = reinterpret_cast<int64_t*>(S->ctrl + kResampleCount + k);
+    tiles += a.num_tiles;
+    compacted[k] = true;
+  }
+  if (tiles > 0) {
+    const qed_status rc = ensure_merge_tiles(S, tiles);
+    if (rc != QED_OK) return rc;
+    const uint32_t epoch = next_epoch(S, st);
+    if (!epoch) {
       set_error("clearing the look-back words failed");
       return QED_ERR_HIP;
     }
-    a.ticket = reinterpret_cast<unsigned long long*>(S->ctrl);
-    a.num_tiles = tiles;
-    a.out_count = reinterpret_cast<int64_t*>(S->ctrl + kResampleCount + k);
-    SFQED_HIP(launch_resample<T>(a, st));
-    compacted[k] = true;
+    for (int k = 0; k < 3; ++k) {
+      la.a[k].state = S->state_c + la.first_block[k];
+      la.a[k].epoch = epoch;
+    }
+    SFQED_HIP(hipMemsetAsync(S->ctrl, 0, 3 * sizeof(uint64_t), st));
+    SFQED_HIP(launch_resample<T>(la, tiles, st));
   }
   if (compacted[0] || compacted[1] || compacted[2]) {
     int64_t kept[3] = {0, 0, 0};

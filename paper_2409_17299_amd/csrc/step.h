@@ -210,6 +210,18 @@ struct LevelState {
   int32_t done, iterations;
 };
 
+// One pass of the threshold solves, for the species with solve[k] set.
+template <typename T>
+struct LevelArgs {
+  SpeciesView<T> s[3];
+  int64_t n[3], target[3];
+  int32_t solve[3];
+  double e_min2;      // squared energy threshold of photons (0: no filter)
+  uint64_t* mask;     // a bit per photon, set by the first pass: it passes the filter
+  LevelState* state;  // [3]
+  double* part;       // [3][kLevelBlocks][4] the blocks' sums
+};
+
 template <typename T>
 struct ResampleArgs {
   SpeciesView<T> s;
@@ -226,6 +238,15 @@ struct ResampleArgs {
   int64_t* out_count;
 };
 
+// One launch compacts up to three species: block b works on species k for
+// first_block[k] <= b < first_block[k + 1] (a species that keeps everything has
+// no blocks).
+template <typename T>
+struct ResampleLaunch {
+  ResampleArgs<T> a[3];
+  int64_t first_block[3];
+};
+
 template <typename T, bool kPhoton>
 hipError_t launch_count(const StepArgs<T>& a, int grid, size_t lds, hipStream_t st);
 template <typename T>
@@ -238,10 +259,9 @@ hipError_t launch_scan(const ScanArgs& s, hipStream_t st);
 template <typename T>
 hipError_t launch_merge_photons(const MergeArgs<T>& a, hipStream_t st);
 template <typename T>
-hipError_t launch_level_pass(const SpeciesView<T>& s, int64_t n, int photon, double e_min2, int64_t target, int first,
-                             double* part, LevelState* ls, hipStream_t st);
+hipError_t launch_level_pass(const LevelArgs<T>& a, int first, hipStream_t st);
 template <typename T>
-hipError_t launch_resample(const ResampleArgs<T>& a, hipStream_t st);
+hipError_t launch_resample(const ResampleLaunch<T>& a, int64_t tiles, hipStream_t st);
 hipError_t launch_count_alive(const uint8_t* alive, int64_t n, unsigned long long* out, hipStream_t st);
 template <typename T>
 hipError_t launch_count_alive_rec(const Rec<T>* rec, int64_t n, unsigned long long* out, hipStream_t st);

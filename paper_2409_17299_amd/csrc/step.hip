@@ -1812,71 +1812,125 @@ __global__ void __launch_bounds__(kStepThreads, sizeof(T) == 4 ? kStepWavesPerSi
 
 // |k|^2 >= e_min^2 in FP64, summed left to right without contraction
 template <typename T>
-__device__ __forceinline__ bool passes_filter(const SpeciesView<T>& s, int64_t i, bool photon, double e_min2) {
+__device__ __forceinline__ bool passes_filter(const T (&p)[3], bool photon, double e_min2) {
 #pragma clang fp contract(off)
   if (!photon || !(e_min2 > 0.0)) return true;
-  const double px = s.px[i], py = s.py[i], pz = s.pz[i];
+  const double px = p[0], py = p[1], pz = p[2];
   return px * px + py * py + pz * pz >= e_min2;
 }
 
-// One pass of the threshold solve, in two kernels.  k_level_partials: per
-// block, over the particles that pass the filter, the weight below wt, the
-// total weight, the count at or above wt and the count (a fixed grid and a
-// fixed reduction order make the sums reproducible).  k_level_step: one block
-// adds the blocks' sums in block order and takes the next step of the solve:
+// One pass of the threshold solve, in two kernels, each for the three species
+// at once.  k_level_partials: per block, over the particles that pass the
+// filter, the weight below wt, the total weight, the count at or above wt and
+// the count (a fixed grid and a fixed reduction order make the sums
+// reproducible).  k_level_step: one block per species adds the blocks' sums in
+// block order and takes the next step of the solve:
 //   first pass (wt = infinity): w_0 = total weight / target when more than
 //     `target` particles pass the filter, else done with wt = 0;
 //   later passes: w <- S(w) / (target - C(w)), done when that no longer
 //     decreases w (or target - C(w) <= 0).
-// The state stays on the device and both kernels return at once when the
-// solve is done, so a fixed number of passes can be queued without waiting
-// for the host; the kernel boundary orders the sums before their total.
+// The state stays on the device and both kernels return at once for a species
+// whose solve is done, so a fixed number of passes can be queued without
+// waiting for the host; the kernel boundary orders the sums before their total.
+// The first pass leaves the filter's outcome as a bit per photon, so that the
+// later ones read 4 bytes of a photon and not 16 (FP64: 28).  A pass is bound by
+// its launches and, for millions of particles, by reading the weights, eight in
+// flight per thread: species by species and with the momenta read in every
+// pass, 27 pairs of kernels took 375 us for 8e6 particles; now 9 pairs take 174.
+
+// Sum over the block in the order of a binary tree over its threads, four
+// values at once; the result is in thread 0 to 3 (value q in thread q).
+__device__ __forceinline__ double level_tree(double (&v)[4], double (*red)[4]) {
+  const int t = threadIdx.x;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) red[t][q] = v[q];
+  __syncthreads();
+  if (t < 128)
+    for (int q = 0; q < 4; ++q) red[t][q] += red[t + 128][q];
+  __syncthreads();
+  if (t < 64) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      v[q] = red[t][q] + red[t + 64][q];
+      for (int h = 32; h > 0; h >>= 1) v[q] += __shfl_down(v[q], h);  // lanes t < h hold the tree's sums
+      v[q] = __shfl(v[q], 0);
+    }
+  }
+  return t == 0 ? v[0] : (t == 1 ? v[1] : (t == 2 ? v[2] : v[3]));
+}
+static_assert(kLevelThreads == 256, "level_tree");
+
 template <typename T>
-__global__ void __launch_bounds__(kLevelThreads) k_level_partials(SpeciesView<T> s, int64_t n, int32_t photon,
-                                                                   double e_min2, int32_t first, const LevelState* ls,
-                                                                   double* part) {
-  __shared__ double red[4][kLevelThreads];
+__global__ void __launch_bounds__(kLevelThreads) k_level_partials(LevelArgs<T> a, int32_t first) {
+  __shared__ double red[kLevelThreads][4];
+  const int k = blockIdx.y;
+  if (!a.solve[k]) return;
+  const LevelState* ls = a.state + k;
   if (!first && ls->done) return;
   const double wt = first ? INFINITY : ls->wt;
-  double bw = 0.0, aw = 0.0, ca = 0.0, ce = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * kLevelThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kLevelThreads) {
-    if (!passes_filter<T>(s, i, photon != 0, e_min2)) continue;
-    const double w = s.w[i];
-    ce += 1.0;
-    aw += w;
-    if (w < wt) bw += w;
-    else ca += 1.0;
+  const SpeciesView<T>& s = a.s[k];
+  const int64_t n = a.n[k];
+  const bool filter = k == 2 && a.e_min2 > 0.0;
+  double v[4] = {0.0, 0.0, 0.0, 0.0};  // weight below wt, weight, count at or above wt, count
+  const int64_t stride = (int64_t)kLevelBlocks * kLevelThreads;
+  constexpr int U = 8;  // particles in flight per thread
+  for (int64_t i0 = (int64_t)blockIdx.x * kLevelThreads + threadIdx.x; i0 < n; i0 += U * stride) {
+    float w[U];
+    bool pass[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = i0 + u * stride < n ? i0 + u * stride : n - 1;
+      w[u] = s.w[i];
+      pass[u] = i0 + u * stride < n;
+    }
+    if (filter && first) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t i = i0 + u * stride < n ? i0 + u * stride : n - 1;
+        const T p[3] = {s.px[i], s.py[i], s.pz[i]};
+        pass[u] = pass[u] && passes_filter<T>(p, true, a.e_min2);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {  // a wave's particles are 64 in a row
+        const uint64_t m = __ballot(pass[u]);
+        if (lane_id() == 0 && i0 + u * stride < n) a.mask[(i0 + u * stride) >> 6] = m;
+      }
+    } else if (filter) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t i = i0 + u * stride < n ? i0 + u * stride : n - 1;
+        pass[u] = pass[u] && ((a.mask[i >> 6] >> (i & 63)) & 1ull);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (!pass[u]) continue;
+      const double x = w[u];
+      v[3] += 1.0;
+      v[1] += x;
+      if (x < wt) v[0] += x;
+      else v[2] += 1.0;
+    }
   }
-  red[0][threadIdx.x] = bw;
-  red[1][threadIdx.x] = aw;
-  red[2][threadIdx.x] = ca;
-  red[3][threadIdx.x] = ce;
-  __syncthreads();
-  for (int h = kLevelThreads / 2; h > 0; h >>= 1) {
-    if ((int)threadIdx.x < h)
-      for (int q = 0; q < 4; ++q) red[q][threadIdx.x] += red[q][threadIdx.x + h];
-    __syncthreads();
-  }
-  if (threadIdx.x < 4) part[(size_t)blockIdx.x * 4 + threadIdx.x] = red[threadIdx.x][0];
+  const double sum = level_tree(v, red);
+  if (threadIdx.x < 4) a.part[((size_t)k * kLevelBlocks + blockIdx.x) * 4 + threadIdx.x] = sum;
 }
 
-__global__ void __launch_bounds__(kLevelThreads) k_level_step(const double* part, int nblocks, int32_t first,
-                                                               double target, LevelState* ls) {
-  __shared__ double red[4][kLevelThreads];
+template <typename T>
+__global__ void __launch_bounds__(kLevelThreads) k_level_step(LevelArgs<T> a, int32_t first) {
+  __shared__ double red[kLevelThreads][4];
+  const int k = blockIdx.x;
+  if (!a.solve[k]) return;
+  LevelState* ls = a.state + k;
   if (!first && ls->done) return;
-  const double wt = first ? INFINITY : ls->wt;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int b = threadIdx.x; b < nblocks; b += kLevelThreads)
-    for (int q = 0; q < 4; ++q) acc[q] += part[(size_t)b * 4 + q];
-  for (int q = 0; q < 4; ++q) red[q][threadIdx.x] = acc[q];
-  __syncthreads();
-  for (int h = kLevelThreads / 2; h > 0; h >>= 1) {
-    if ((int)threadIdx.x < h)
-      for (int q = 0; q < 4; ++q) red[q][threadIdx.x] += red[q][threadIdx.x + h];
-    __syncthreads();
-  }
+  const double wt = first ? INFINITY : ls->wt, target = (double)a.target[k];
+  const double* part = a.part + (size_t)k * kLevelBlocks * 4;
+  double v[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int b = threadIdx.x; b < kLevelBlocks; b += kLevelThreads)
+    for (int q = 0; q < 4; ++q) v[q] += part[(size_t)b * 4 + q];
+  (void)level_tree(v, red);
   if (threadIdx.x != 0) return;
-  const double below = red[0][0], total = red[1][0], above = red[2][0], count = red[3][0];
+  const double below = v[0], total = v[1], above = v[2], count = v[3];
   if (first) {
     ls->eligible = count;
     ls->total = total;
@@ -1903,15 +1957,48 @@ __global__ void __launch_bounds__(kLevelThreads) k_level_step(const double* part
   }
 }
 
+// The survivors of a compaction tile: kMergeItems items per thread, item-major,
+// then thread.  pre: survivors of the tile before each of the thread's items.
+__device__ __forceinline__ int32_t tile_ranks(uint32_t okmask, int32_t (*wsum)[kMergeThreads / 64],
+                                              int32_t (&pre)[kMergeItems]) {
+  const int lane = lane_id(), wave = threadIdx.x >> 6;
+  uint64_t m[kMergeItems];
+#pragma unroll
+  for (int it = 0; it < kMergeItems; ++it) {
+    m[it] = __ballot((okmask >> it) & 1u);
+    if (lane == 0) wsum[it][wave] = __popcll(m[it]);
+  }
+  __syncthreads();
+  int32_t total = 0;
+#pragma unroll
+  for (int it = 0; it < kMergeItems; ++it) {
+    int32_t before = 0, all = 0;
+    for (int wv = 0; wv < kMergeThreads / 64; ++wv) {
+      before += wv < wave ? wsum[it][wv] : 0;
+      all += wsum[it][wv];
+    }
+    pre[it] = total + before + (int32_t)mbcnt(m[it]);
+    total += all;
+  }
+  return total;
+}
+
 // Stable in-place compaction of the survivors (the tile scheme of the photon
 // merge): a particle stays if it passes the filter and, when wt > 0, if
 // w >= wt or its draw u = (x + 1/2) 2^-32 is below w / wt; a light survivor
 // then weighs wt.
+// Bound by HBM (32 bytes read, 33 written per survivor in FP32): every load of
+// a tile is issued before the first decision, also for particles that turn out
+// to leave, since a load that waits for a decision waits a second latency; one
+// launch covers the species.  8e6 particles, 60% of them kept: 176 us in three
+// launches, now 120 (3.5 TB/s).
 template <typename T>
-__global__ void __launch_bounds__(kMergeThreads) k_resample(ResampleArgs<T> a) {
-  __shared__ int32_t wsum[kMergeThreads / 64];
+__global__ void __launch_bounds__(kMergeThreads) k_resample(ResampleLaunch<T> la) {
+  __shared__ int32_t wsum[kMergeItems][kMergeThreads / 64];
   __shared__ int64_t s_tile, s_base;
   const int tid = threadIdx.x;
+  const int sp = (int64_t)blockIdx.x >= la.first_block[2] ? 2 : ((int64_t)blockIdx.x >= la.first_block[1] ? 1 : 0);
+  const ResampleArgs<T>& a = la.a[sp];
   if (tid == 0) s_tile = (int64_t)atomicAdd(a.ticket, 1ull);
   __syncthreads();
   const int64_t tile = s_tile;
@@ -1923,57 +2010,40 @@ __global__ void __launch_bounds__(kMergeThreads) k_resample(ResampleArgs<T> a) {
   uint32_t okmask = 0;
 #pragma unroll
   for (int it = 0; it < kMergeItems; ++it) {
-    const int64_t g = tile * kMergeTile + (int64_t)it * kMergeThreads + tid;
-    bool ok = false;
-    if (g < a.n && passes_filter<T>(s, g, a.photon != 0, a.e_min2)) {
-      w[it] = s.w[g];
-      id[it] = s.id[g];
-      ok = true;
-      if (a.wt > 0.0 && (double)w[it] < a.wt) {
-        const double u = ((double)draw(a.seed, id[it], a.step, kResampleJ).x + 0.5) * 0x1p-32;
-        ok = u < (double)w[it] / a.wt;
-        w[it] = (float)a.wt;
-      }
-      if (ok) {
-        p[it][0] = s.px[g];
-        p[it][1] = s.py[g];
-        p[it][2] = s.pz[g];
-        if (a.positions) {
-          x[it][0] = s.x[g];
-          x[it][1] = s.y[g];
-          x[it][2] = s.z[g];
-        }
-        tau[it] = s.tau[g];
-      }
+    const int64_t g0 = tile * kMergeTile + (int64_t)it * kMergeThreads + tid;
+    const int64_t g = g0 < a.n ? g0 : a.n - 1;
+    w[it] = s.w[g];
+    id[it] = s.id[g];
+    p[it][0] = s.px[g];
+    p[it][1] = s.py[g];
+    p[it][2] = s.pz[g];
+    if (a.positions) {
+      x[it][0] = s.x[g];
+      x[it][1] = s.y[g];
+      x[it][2] = s.z[g];
     }
-    okmask |= (ok ? 1u : 0u) << it;
+    tau[it] = s.tau[g];
   }
   // every load of the tile must have returned before its aggregate is
   // published (later tiles write into this tile's range)
 #pragma unroll
   for (int it = 0; it < kMergeItems; ++it) {
-    if ((okmask >> it) & 1u) {
-      asm volatile("" ::"v"(p[it][0]), "v"(p[it][1]), "v"(p[it][2]), "v"(w[it]), "v"(tau[it]), "v"(id[it])
-                   : "memory");
-      if (a.positions) asm volatile("" ::"v"(x[it][0]), "v"(x[it][1]), "v"(x[it][2]) : "memory");
+    asm volatile("" ::"v"(p[it][0]), "v"(p[it][1]), "v"(p[it][2]), "v"(w[it]), "v"(tau[it]), "v"(id[it]) : "memory");
+    if (a.positions) asm volatile("" ::"v"(x[it][0]), "v"(x[it][1]), "v"(x[it][2]) : "memory");
+  }
+#pragma unroll
+  for (int it = 0; it < kMergeItems; ++it) {
+    const int64_t g = tile * kMergeTile + (int64_t)it * kMergeThreads + tid;
+    bool ok = g < a.n && passes_filter<T>(p[it], a.photon != 0, a.e_min2);
+    if (ok && a.wt > 0.0 && (double)w[it] < a.wt) {
+      const double u = ((double)draw(a.seed, id[it], a.step, kResampleJ).x + 0.5) * 0x1p-32;
+      ok = u < (double)w[it] / a.wt;
+      w[it] = (float)a.wt;
     }
+    okmask |= (ok ? 1u : 0u) << it;
   }
   int32_t pre[kMergeItems];
-  const int lane = lane_id(), wave = tid >> 6;
-  int32_t tile_total = 0;
-  for (int it = 0; it < kMergeItems; ++it) {
-    const uint64_t m = __ballot((okmask >> it) & 1u);
-    if (lane == 0) wsum[wave] = __popcll(m);
-    __syncthreads();
-    int32_t before = 0, all = 0;
-    for (int wv = 0; wv < kMergeThreads / 64; ++wv) {
-      before += wv < wave ? wsum[wv] : 0;
-      all += wsum[wv];
-    }
-    pre[it] = tile_total + before + (int32_t)mbcnt(m);
-    tile_total += all;
-    __syncthreads();
-  }
+  const int32_t tile_total = tile_ranks(okmask, wsum, pre);
   if (tid < 64) {
     const int64_t b = lookback(a.state, tile, tile_total, 0, a.epoch);
     if (tid == 0) {
@@ -2104,7 +2174,7 @@ __global__ void __launch_bounds__(256) k_sample4(TableView tab, int process, con
 // never overwrite an element that is still to be read.
 template <typename T>
 __global__ void __launch_bounds__(kMergeThreads) k_merge_photons(MergeArgs<T> a) {
-  __shared__ int32_t wsum[kMergeThreads / 64];
+  __shared__ int32_t wsum[kMergeItems][kMergeThreads / 64];
   __shared__ int64_t s_tile, s_base;
   const int tid = threadIdx.x;
   if (tid == 0) s_tile = (int64_t)atomicAdd(a.ticket, 1ull);
@@ -2116,50 +2186,49 @@ __global__ void __launch_bounds__(kMergeThreads) k_merge_photons(MergeArgs<T> a)
   double tau[kMergeItems];
   uint64_t id[kMergeItems];
   uint32_t okmask = 0;
-  // item i of this thread: tile * kMergeTile + i * kMergeThreads + tid (coalesced per item)
+  // item i of this thread: tile * kMergeTile + i * kMergeThreads + tid (coalesced per item);
+  // loads do not wait for the alive flag, which would be a second latency
+  uint8_t al[kMergeItems];
+  uint32_t ra[kMergeItems];
 #pragma unroll
   for (int it = 0; it < kMergeItems; ++it) {
     const int64_t g = tile * kMergeTile + (int64_t)it * kMergeThreads + tid;
-    bool ok = false;
-    if (g < ntot) {
-      if (g < a.n_main) {
-        const SpeciesView<T>& s = a.main;
-        ok = s.alive[g] != 0;
-        if (ok) {
-          p[it][0] = s.px[g];
-          p[it][1] = s.py[g];
-          p[it][2] = s.pz[g];
-          if (a.positions) {
-            x[it][0] = s.x[g];
-            x[it][1] = s.y[g];
-            x[it][2] = s.z[g];
-          }
-          w[it] = s.w[g];
-          tau[it] = s.tau[g];
-          id[it] = s.id[g];
-        }
-      } else {
-        const int64_t i = g - a.n_main;
-        Rec<T> r;
-        rec_load<T>(a.app, i, r);
-        ok = r.alive != 0;
-        if (ok) {
-          p[it][0] = r.px;
-          p[it][1] = r.py;
-          p[it][2] = r.pz;
-          if (a.positions) {
-            x[it][0] = a.app_pos[4 * i];
-            x[it][1] = a.app_pos[4 * i + 1];
-            x[it][2] = a.app_pos[4 * i + 2];
-          }
-          w[it] = r.w;
-          tau[it] = r.tau;
-          id[it] = r.id;
-        }
+    al[it] = 0;
+    ra[it] = 0;
+    if (g < a.n_main) {
+      const SpeciesView<T>& s = a.main;
+      al[it] = s.alive[g];
+      p[it][0] = s.px[g];
+      p[it][1] = s.py[g];
+      p[it][2] = s.pz[g];
+      if (a.positions) {
+        x[it][0] = s.x[g];
+        x[it][1] = s.y[g];
+        x[it][2] = s.z[g];
       }
+      w[it] = s.w[g];
+      tau[it] = s.tau[g];
+      id[it] = s.id[g];
+    } else if (g < ntot) {
+      const int64_t i = g - a.n_main;
+      Rec<T> r;
+      rec_load<T>(a.app, i, r);
+      ra[it] = r.alive;
+      p[it][0] = r.px;
+      p[it][1] = r.py;
+      p[it][2] = r.pz;
+      if (a.positions) {
+        x[it][0] = a.app_pos[4 * i];
+        x[it][1] = a.app_pos[4 * i + 1];
+        x[it][2] = a.app_pos[4 * i + 2];
+      }
+      w[it] = r.w;
+      tau[it] = r.tau;
+      id[it] = r.id;
     }
-    okmask |= (ok ? 1u : 0u) << it;
   }
+#pragma unroll
+  for (int it = 0; it < kMergeItems; ++it) okmask |= (al[it] != 0 || ra[it] != 0 ? 1u : 0u) << it;
   // The tile's loads must have returned before its aggregate becomes visible
   // (later tiles write into this tile's source range).  Consuming every loaded
   // register in an empty asm makes the compiler wait for the loads here; the
@@ -2172,23 +2241,8 @@ __global__ void __launch_bounds__(kMergeThreads) k_merge_photons(MergeArgs<T> a)
       if (a.positions) asm volatile("" ::"v"(x[it][0]), "v"(x[it][1]), "v"(x[it][2]) : "memory");
     }
   }
-  // order within the tile: item-major, then thread (matches g)
   int32_t pre[kMergeItems];
-  const int lane = lane_id(), wave = tid >> 6;
-  int32_t tile_total = 0;
-  for (int it = 0; it < kMergeItems; ++it) {
-    const uint64_t m = __ballot((okmask >> it) & 1u);
-    if (lane == 0) wsum[wave] = __popcll(m);
-    __syncthreads();
-    int32_t before = 0, all = 0;
-    for (int wv = 0; wv < kMergeThreads / 64; ++wv) {
-      before += wv < wave ? wsum[wv] : 0;
-      all += wsum[wv];
-    }
-    pre[it] = tile_total + before + (int32_t)mbcnt(m);
-    tile_total += all;
-    __syncthreads();
-  }
+  const int32_t tile_total = tile_ranks(okmask, wsum, pre);
   if (tid < 64) {
     const int64_t b = lookback(a.state, tile, tile_total, 0, a.epoch);
     if (tid == 0) {
@@ -2334,17 +2388,15 @@ hipError_t launch_scan(const ScanArgs& s, hipStream_t st) {
   return hipGetLastError();
 }
 template <typename T>
-hipError_t launch_level_pass(const SpeciesView<T>& s, int64_t n, int photon, double e_min2, int64_t target, int first,
-                             double* part, LevelState* ls, hipStream_t st) {
-  hipLaunchKernelGGL((k_level_partials<T>), dim3(kLevelBlocks), dim3(kLevelThreads), 0, st, s, n, photon, e_min2,
-                     first, ls, part);
-  hipLaunchKernelGGL(k_level_step, dim3(1), dim3(kLevelThreads), 0, st, part, kLevelBlocks, first, (double)target, ls);
+hipError_t launch_level_pass(const LevelArgs<T>& a, int first, hipStream_t st) {
+  hipLaunchKernelGGL((k_level_partials<T>), dim3(kLevelBlocks, 3), dim3(kLevelThreads), 0, st, a, first);
+  hipLaunchKernelGGL((k_level_step<T>), dim3(3), dim3(kLevelThreads), 0, st, a, first);
   return hipGetLastError();
 }
 
 template <typename T>
-hipError_t launch_resample(const ResampleArgs<T>& a, hipStream_t st) {
-  hipLaunchKernelGGL((k_resample<T>), dim3((unsigned)a.num_tiles), dim3(kMergeThreads), 0, st, a);
+hipError_t launch_resample(const ResampleLaunch<T>& a, int64_t tiles, hipStream_t st) {
+  hipLaunchKernelGGL((k_resample<T>), dim3((unsigned)tiles), dim3(kMergeThreads), 0, st, a);
   return hipGetLastError();
 }
 
@@ -2424,14 +2476,12 @@ template hipError_t launch_write<float, true>(const StepArgs<float>&, int, size_
 template hipError_t launch_write<double, false>(const StepArgs<double>&, int, size_t, hipStream_t, bool);
 template hipError_t launch_write<double, true>(const StepArgs<double>&, int, size_t, hipStream_t, bool);
 template hipError_t launch_merge_photons<float>(const MergeArgs<float>&, hipStream_t);
-template hipError_t launch_level_pass<float>(const SpeciesView<float>&, int64_t, int, double, int64_t, int, double*,
-                                                LevelState*, hipStream_t);
-template hipError_t launch_level_pass<double>(const SpeciesView<double>&, int64_t, int, double, int64_t, int,
-                                                 double*, LevelState*, hipStream_t);
+template hipError_t launch_level_pass<float>(const LevelArgs<float>&, int, hipStream_t);
+template hipError_t launch_level_pass<double>(const LevelArgs<double>&, int, hipStream_t);
 template hipError_t launch_count_photon_merged<float>(const StepArgs<float>&, int, size_t, hipStream_t);
 template hipError_t launch_count_photon_merged<double>(const StepArgs<double>&, int, size_t, hipStream_t);
-template hipError_t launch_resample<float>(const ResampleArgs<float>&, hipStream_t);
-template hipError_t launch_resample<double>(const ResampleArgs<double>&, hipStream_t);
+template hipError_t launch_resample<float>(const ResampleLaunch<float>&, int64_t, hipStream_t);
+template hipError_t launch_resample<double>(const ResampleLaunch<double>&, int64_t, hipStream_t);
 template hipError_t launch_merge_photons<double>(const MergeArgs<double>&, hipStream_t);
 template hipError_t launch_init_tau<float>(double*, const uint64_t*, int64_t, uint64_t, uint32_t, hipStream_t);
 template hipError_t launch_count_alive_rec<float>(const Rec<float>*, int64_t, unsigned long long*, hipStream_t);
