@@ -625,7 +625,18 @@ qed_status step_impl(const qed_tables* tab, const qed_step_cfg* cfg, qed_ensembl
   qed_step_stats local;
   std::memset(&local, 0, sizeof(local));
   int64_t cur[2] = {0, 0};  // photons, leptons appended so far
-  auto read_cursors = [&]() -> qed_status { return read_back(S, cur, S->ctrl + kCurPhoton, sizeof(cur), st); };
+  // One copy per read-back brings all a round or the end of the step needs: the
+  // cursors, the statistics and the merged photon cursor.  (A read-back costs
+  // 20 to 30 us of an idle GPU; the last two used to be copies of their own.)
+  constexpr int kWords = kMergedCursor - kCurPhoton + 1;
+  static_assert(kWords * sizeof(uint64_t) <= kPinBytes, "one pinned read-back");
+  uint64_t words[kWords] = {};
+  auto read_cursors = [&]() -> qed_status {
+    const qed_status r = read_back(S, words, S->ctrl + kCurPhoton, sizeof(words), st);
+    cur[0] = (int64_t)words[0];
+    cur[1] = (int64_t)words[kCurLepton - kCurPhoton];
+    return r;
+  };
   const int64_t capg = app[2].capacity, capl = std::min(app[0].capacity, app[1].capacity);
   EventLog log;
   log.on = cfg->profile != 0;
@@ -650,6 +661,24 @@ qed_status step_impl(const qed_tables* tab, const qed_step_cfg* cfg, qed_ensembl
     ++launches;
     return run_launch<T>(S, st, tab, cfg, ens, app, 2, false, g_from, capg - g_from, 0, 0, dt, seed, step, &slot,
                          positions, log, &local, true, true);
+  };
+  // Merged: the records of leptons [from, to) are in their final state once
+  // their round has run, and go after the input leptons while the round's
+  // read-back is still to come (unless they do not fit, which the end reports).
+  auto append_leptons = [&](int64_t from, int64_t to) -> qed_status {
+    if (!merged || to <= from || ens->s[0].count + to > ens->s[0].capacity ||
+        ens->s[1].count + to > ens->s[1].capacity)
+      return QED_OK;
+    AppendArgs<T> ap;
+    for (int s = 0; s < 2; ++s) {
+      ap.dst[s] = view_of<T>(ens->s[s]);
+      ap.at[s] = ens->s[s].count + from;
+      ap.rec[s] = static_cast<const Rec<T>*>(app[s].rec) + from;
+      ap.pos[s] = positions ? static_cast<const T*>(app[s].pos) + 4 * from : nullptr;
+      ap.n[s] = to - from;
+    }
+    SFQED_HIP(launch_append_records<T>(ap, st));
+    return QED_OK;
   };
   // after the round's read-back: the appended photons the round processed
   auto photons_done = [&](int64_t g_from) -> int64_t {
@@ -705,7 +734,7 @@ qed_status step_impl(const qed_tables* tab, const qed_step_cfg* cfg, qed_ensembl
   }
   int64_t rounds = 1, l_done = 0;
   while (!overflow && cur[1] > l_done) {
-    const int64_t l_hi = cur[1];
+    const int64_t l_from = l_done, l_hi = cur[1];
     if ((rc = launch(0, false, l_done, l_hi - l_done, l_done, l_hi - l_done)) != QED_OK) return rc;
     l_done = l_hi;
     if (!merged) {
@@ -716,13 +745,13 @@ qed_status step_impl(const qed_tables* tab, const qed_step_cfg* cfg, qed_ensembl
       }
     }
     if ((rc = launch_appended_photons(g_done)) != QED_OK) return rc;
+    if ((rc = append_leptons(l_from, l_hi)) != QED_OK) return rc;
     if ((rc = read_cursors()) != QED_OK) return rc;
     g_done = photons_done(g_done);
     overflow = cur[0] > capg || cur[1] > capl;
     ++rounds;
   }
-  uint64_t dev_stats[8];
-  if ((rc = read_back(S, dev_stats, S->ctrl + kStats, sizeof(dev_stats), st)) != QED_OK) return rc;
+  const uint64_t* dev_stats = words + (kStats - kCurPhoton);
   grow_log(S, dev_stats[kStatLogNeed]);  // later steps replay launches this one had to re-run
   local.n_emit = cur[0];
   local.n_pair = cur[1];
@@ -750,20 +779,14 @@ qed_status step_impl(const qed_tables* tab, const qed_step_cfg* cfg, qed_ensembl
     return QED_ERR_CAPACITY;
   }
   if (merged) {
-    // the photons are merged; the leptons' records go after the input leptons
-    int64_t photons = 0;
-    if ((rc = read_back(S, &photons, S->ctrl + kMergedCursor, sizeof(int64_t), st)) != QED_OK) return rc;
+    // the photons are merged and the leptons' records appended, round by round
+    const int64_t photons = (int64_t)words[kMergedCursor - kCurPhoton];
     if (ens->s[0].count + app[0].count > ens->s[0].capacity || ens->s[1].count + app[1].count > ens->s[1].capacity ||
         photons > ens->s[2].capacity) {
       ens->s[2].count = std::min(photons, ens->s[2].capacity);
       set_error("merged step: main capacity exceeded (photons " + std::to_string(photons) + ")");
       return QED_ERR_CAPACITY;
     }
-    for (int s = 0; s < 2; ++s)
-      SFQED_HIP(launch_append_records<T>(view_of<T>(ens->s[s]), ens->s[s].count,
-                                         static_cast<const Rec<T>*>(app[s].rec), static_cast<const T*>(app[s].pos),
-                                         app[s].count, positions ? 1 : 0, st));
-    SFQED_HIP(hipStreamSynchronize(st));
     ens->s[0].count += app[0].count;
     ens->s[1].count += app[1].count;
     ens->s[2].count = photons;
@@ -815,9 +838,15 @@ qed_status merge_on(qed_ensemble* ens, const qed_append* app, hipStream_t st, co
       return QED_ERR_CAPACITY;
     }
   }
-  for (int s = 0; s < 2; ++s)
-    SFQED_HIP(launch_append_records<T>(view_of<T>(ens->s[s]), ens->s[s].count, static_cast<const Rec<T>*>(app[s].rec),
-                                       static_cast<const T*>(app[s].pos), app[s].count, positions ? 1 : 0, st));
+  AppendArgs<T> ap;
+  for (int s = 0; s < 2; ++s) {
+    ap.dst[s] = view_of<T>(ens->s[s]);
+    ap.at[s] = ens->s[s].count;
+    ap.rec[s] = static_cast<const Rec<T>*>(app[s].rec);
+    ap.pos[s] = positions ? static_cast<const T*>(app[s].pos) : nullptr;
+    ap.n[s] = app[s].count;
+  }
+  SFQED_HIP(launch_append_records<T>(ap, st));
   int64_t new_photons = 0;
   if (ntot > 0) {
     MergeArgs<T> m;
@@ -934,10 +963,55 @@ qed_status resample_impl(qed_ensemble* ens, const qed_resample_cfg* cfg, qed_res
     if (rc != QED_OK) return rc;
     lv.mask = reinterpret_cast<uint64_t*>(S->offsets);
   }
-  for (int q = 0; q < passes; ++q) SFQED_HIP(launch_level_pass<T>(lv, q == 0 ? 1 : 0, st));
-  LevelState ls[3];
-  qed_status rb = read_back(S, ls, dstate, sizeof(ls), st);
+  // The compaction follows the passes without a wait between: it takes each
+  // threshold from the device, and does nothing while a solve has not finished
+  // (the host then goes on with that solve and launches it again).
+  ResampleLaunch<T> la;
+  std::memset(&la, 0, sizeof(la));
+  la.state = dstate;
+  int64_t tiles = 0;
+  for (int k = 0; k < 3; ++k) {
+    la.first_block[k] = tiles;
+    if (!lv.solve[k]) continue;
+    ResampleArgs<T>& a = la.a[k];
+    a.s = lv.s[k];
+    a.n = lv.n[k];
+    a.photon = k == 2 ? 1 : 0;
+    a.positions = positions ? 1 : 0;
+    a.e_min2 = k == 2 ? e_min2 : 0.0;
+    a.seed = cfg->seed;
+    a.step = cfg->step;
+    a.num_tiles = (a.n + kMergeTile - 1) / kMergeTile;
+    tiles += a.num_tiles;
+    la.solve[k] = 1;
+  }
+  if (tiles == 0) {
+    if (out) *out = stats;
+    return QED_OK;
+  }
+  qed_status rb = ensure_merge_tiles(S, tiles);
   if (rb != QED_OK) return rb;
+  auto compact = [&](int forced) -> qed_status {
+    la.forced = forced;
+    const uint32_t epoch = next_epoch(S, st);
+    if (!epoch) {
+      set_error("clearing the look-back words failed");
+      return QED_ERR_HIP;
+    }
+    for (int k = 0; k < 3; ++k) {
+      la.a[k].state = S->state_c + la.first_block[k];
+      la.a[k].epoch = epoch;
+      la.a[k].ticket = reinterpret_cast<unsigned long long*>(S->ctrl + k);
+    }
+    SFQED_HIP(hipMemsetAsync(S->ctrl, 0, 8 * sizeof(uint64_t), st));
+    SFQED_HIP(launch_resample<T>(la, tiles, st));
+    return QED_OK;
+  };
+  for (int q = 0; q < passes; ++q) SFQED_HIP(launch_level_pass<T>(lv, q == 0 ? 1 : 0, st));
+  if ((rb = compact(0)) != QED_OK) return rb;
+  LevelState ls[3];
+  if ((rb = read_back(S, ls, dstate, sizeof(ls), st)) != QED_OK) return rb;
+  bool late = false;
   // solves that have not finished go on one pass at a time
   while (true) {
     LevelArgs<T> more = lv;
@@ -947,62 +1021,24 @@ qed_status resample_impl(qed_ensemble* ens, const qed_resample_cfg* cfg, qed_res
       any |= more.solve[k] != 0;
     }
     if (!any) break;
+    late = true;
     SFQED_HIP(launch_level_pass<T>(more, 0, st));
+    if ((rb = read_back(S, ls, dstate, sizeof(ls), st)) != QED_OK) return rb;
+  }
+  for (int k = 0; k < 3; ++k) late |= lv.solve[k] && !ls[k].done;  // stopped at the limit of passes
+  if (late) {
+    if ((rb = compact(1)) != QED_OK) return rb;
     if ((rb = read_back(S, ls, dstate, sizeof(ls), st)) != QED_OK) return rb;
   }
   for (int k = 0; k < 3; ++k)
     if (lv.solve[k] && cfg->target[k] > 0)
       S->level_passes[k] = std::max(2, std::min(kLevelDevicePasses, ls[k].iterations + 1));
-  bool compacted[3] = {false, false, false};
-  ResampleLaunch<T> la;
-  std::memset(&la, 0, sizeof(la));
-  int64_t tiles = 0;
   for (int k = 0; k < 3; ++k) {
-    la.first_block[k] = tiles;
     if (!lv.solve[k]) continue;
-    const int64_t n = ens->s[k].count;
-    const bool photon = k == 2, filter = photon && e_min2 > 0.0;
-    const int64_t eligible = (int64_t)ls[k].eligible;
-    const double wt = ls[k].wt;
     stats.iterations[k] = ls[k].iterations;
-    stats.w_threshold[k] = wt;
-    if (photon) stats.filtered = n - eligible;
-    if (wt <= 0.0 && !(filter && eligible < n)) continue;  // nothing to remove
-    ResampleArgs<T>& a = la.a[k];
-    a.s = view_of<T>(ens->s[k]);
-    a.n = n;
-    a.photon = photon ? 1 : 0;
-    a.positions = positions ? 1 : 0;
-    a.e_min2 = filter ? e_min2 : 0.0;
-    a.wt = wt;
-    a.seed = cfg->seed;
-    a.step = cfg->step;
-    a.ticket = reinterpret_cast<unsigned long long*>(S->ctrl + k);
-    a.num_tiles = (n + kMergeTile - 1) / kMergeTile;
-    a.out_count = reinterpret_cast<int64_t*>(S->ctrl + kResampleCount + k);
-    tiles += a.num_tiles;
-    compacted[k] = true;
-  }
-  if (tiles > 0) {
-    const qed_status rc = ensure_merge_tiles(S, tiles);
-    if (rc != QED_OK) return rc;
-    const uint32_t epoch = next_epoch(S, st);
-    if (!epoch) {
-      set_error("clearing the look-back words failed");
-      return QED_ERR_HIP;
-    }
-    for (int k = 0; k < 3; ++k) {
-      la.a[k].state = S->state_c + la.first_block[k];
-      la.a[k].epoch = epoch;
-    }
-    SFQED_HIP(hipMemsetAsync(S->ctrl, 0, 3 * sizeof(uint64_t), st));
-    SFQED_HIP(launch_resample<T>(la, tiles, st));
-  }
-  if (compacted[0] || compacted[1] || compacted[2]) {
-    int64_t kept[3] = {0, 0, 0};
-    if ((rb = read_back(S, kept, S->ctrl + kResampleCount, sizeof(kept), st)) != QED_OK) return rb;
-    for (int k = 0; k < 3; ++k)
-      if (compacted[k]) ens->s[k].count = stats.count_after[k] = kept[k];
+    stats.w_threshold[k] = ls[k].wt;
+    if (k == 2) stats.filtered = lv.n[k] - (int64_t)ls[k].eligible;
+    ens->s[k].count = stats.count_after[k] = ls[k].kept;
   }
   if (out) *out = stats;
   return QED_OK;

@@ -206,7 +206,7 @@ struct LevelState {
   double wt;        // current threshold weight (0: no thinning)
   double eligible;  // particles that pass the filter
   double total;     // their total weight
-  double pad;
+  int64_t kept;     // particles after the compaction (written by k_resample)
   int32_t done, iterations;
 };
 
@@ -228,14 +228,12 @@ struct ResampleArgs {
   int64_t n;
   int32_t photon, positions;
   double e_min2;  // squared energy threshold of photons (0: no filter)
-  double wt;      // leveling threshold weight (0: no leveling)
   uint64_t seed;
   uint32_t step;
   uint64_t* state;
   uint32_t epoch;
   unsigned long long* ticket;
   int64_t num_tiles;
-  int64_t* out_count;
 };
 
 // One launch compacts up to three species: block b works on species k for
@@ -245,6 +243,19 @@ template <typename T>
 struct ResampleLaunch {
   ResampleArgs<T> a[3];
   int64_t first_block[3];
+  int32_t solve[3];
+  int32_t forced;     // 0: nothing is done unless the solves of all these species have finished
+  LevelState* state;  // [3]: the thresholds
+};
+
+// The records of both lepton species behind the particles of their arrays.
+template <typename T>
+struct AppendArgs {
+  SpeciesView<T> dst[2];
+  int64_t at[2];  // first free place
+  const Rec<T>* rec[2];
+  const T* pos[2];  // or null
+  int64_t n[2];
 };
 
 template <typename T, bool kPhoton>
@@ -266,8 +277,7 @@ hipError_t launch_count_alive(const uint8_t* alive, int64_t n, unsigned long lon
 template <typename T>
 hipError_t launch_count_alive_rec(const Rec<T>* rec, int64_t n, unsigned long long* out, hipStream_t st);
 template <typename T>
-hipError_t launch_append_records(const SpeciesView<T>& dst, int64_t at, const Rec<T>* rec, const T* pos, int64_t n,
-                                 int positions, hipStream_t st);
+hipError_t launch_append_records(const AppendArgs<T>& a, hipStream_t st);
 // particles of [0, n) with a non-finite momentum, position, weight, optical
 // depth or field component are added to *bad (validate.hip)
 template <typename T>

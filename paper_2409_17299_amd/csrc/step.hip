@@ -1999,6 +1999,15 @@ __global__ void __launch_bounds__(kMergeThreads) k_resample(ResampleLaunch<T> la
   const int tid = threadIdx.x;
   const int sp = (int64_t)blockIdx.x >= la.first_block[2] ? 2 : ((int64_t)blockIdx.x >= la.first_block[1] ? 1 : 0);
   const ResampleArgs<T>& a = la.a[sp];
+  bool finished = true;
+  for (int k = 0; k < 3; ++k) finished &= !la.solve[k] || la.state[k].done;
+  if (!finished && !la.forced) return;
+  LevelState* ls = la.state + sp;
+  const double wt = ls->wt;  // leveling threshold weight (0: no leveling)
+  if (wt <= 0.0 && !(a.e_min2 > 0.0 && (int64_t)ls->eligible < a.n)) {  // nothing to remove
+    if ((int64_t)blockIdx.x == la.first_block[sp] && tid == 0) ls->kept = a.n;
+    return;
+  }
   if (tid == 0) s_tile = (int64_t)atomicAdd(a.ticket, 1ull);
   __syncthreads();
   const int64_t tile = s_tile;
@@ -2035,10 +2044,10 @@ __global__ void __launch_bounds__(kMergeThreads) k_resample(ResampleLaunch<T> la
   for (int it = 0; it < kMergeItems; ++it) {
     const int64_t g = tile * kMergeTile + (int64_t)it * kMergeThreads + tid;
     bool ok = g < a.n && passes_filter<T>(p[it], a.photon != 0, a.e_min2);
-    if (ok && a.wt > 0.0 && (double)w[it] < a.wt) {
+    if (ok && wt > 0.0 && (double)w[it] < wt) {
       const double u = ((double)draw(a.seed, id[it], a.step, kResampleJ).x + 0.5) * 0x1p-32;
-      ok = u < (double)w[it] / a.wt;
-      w[it] = (float)a.wt;
+      ok = u < (double)w[it] / wt;
+      w[it] = (float)wt;
     }
     okmask |= (ok ? 1u : 0u) << it;
   }
@@ -2048,7 +2057,7 @@ __global__ void __launch_bounds__(kMergeThreads) k_resample(ResampleLaunch<T> la
     const int64_t b = lookback(a.state, tile, tile_total, 0, a.epoch);
     if (tid == 0) {
       s_base = b;
-      if (tile == a.num_tiles - 1) *a.out_count = b + tile_total;
+      if (tile == a.num_tiles - 1) ls->kept = b + tile_total;
     }
   }
   __syncthreads();
@@ -2289,25 +2298,27 @@ __global__ void k_count_alive_rec(const Rec<T>* rec, int64_t n, unsigned long lo
   if (lane_id() == 0 && c) atomicAdd(out, (unsigned long long)c);
 }
 
-// Appends n records after position `at` of a species' arrays (leptons: all
-// survive, so this is a plain conversion of the records).
+// Appends records after position `at` of both lepton species' arrays (leptons:
+// all survive, so this is a plain conversion of the records).
 template <typename T>
-__global__ void k_append_records(SpeciesView<T> d, int64_t at, const Rec<T>* rec, const T* pos, int64_t n,
-                                 int positions) {
+__global__ void k_append_records(AppendArgs<T> a) {
+  const int s = blockIdx.y;
+  const SpeciesView<T>& d = a.dst[s];
+  const int64_t n = a.n[s];
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
     Rec<T> r;
-    rec_load<T>(rec, i, r);
-    const int64_t o = at + i;
+    rec_load<T>(a.rec[s], i, r);
+    const int64_t o = a.at[s] + i;
     d.px[o] = r.px;
     d.py[o] = r.py;
     d.pz[o] = r.pz;
     d.w[o] = r.w;
     d.tau[o] = r.tau;
     d.id[o] = r.id;
-    if (positions) {
-      d.x[o] = pos[4 * i];
-      d.y[o] = pos[4 * i + 1];
-      d.z[o] = pos[4 * i + 2];
+    if (a.pos[s]) {
+      d.x[o] = a.pos[s][4 * i];
+      d.y[o] = a.pos[s][4 * i + 1];
+      d.z[o] = a.pos[s][4 * i + 2];
     }
   }
 }
@@ -2421,12 +2432,12 @@ hipError_t launch_count_alive_rec(const Rec<T>* rec, int64_t n, unsigned long lo
   return hipGetLastError();
 }
 template <typename T>
-hipError_t launch_append_records(const SpeciesView<T>& dst, int64_t at, const Rec<T>* rec, const T* pos, int64_t n,
-                                 int positions, hipStream_t st) {
+hipError_t launch_append_records(const AppendArgs<T>& a, hipStream_t st) {
+  const int64_t n = a.n[0] > a.n[1] ? a.n[0] : a.n[1];
   if (n <= 0) return hipSuccess;
   int grid = (int)((n + 255) / 256);
-  grid = grid > 8192 ? 8192 : grid;
-  hipLaunchKernelGGL(k_append_records<T>, dim3(grid), dim3(256), 0, st, dst, at, rec, pos, n, positions);
+  grid = grid > 4096 ? 4096 : grid;
+  hipLaunchKernelGGL(k_append_records<T>, dim3(grid, 2), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 template <typename T>
@@ -2486,10 +2497,8 @@ template hipError_t launch_merge_photons<double>(const MergeArgs<double>&, hipSt
 template hipError_t launch_init_tau<float>(double*, const uint64_t*, int64_t, uint64_t, uint32_t, hipStream_t);
 template hipError_t launch_count_alive_rec<float>(const Rec<float>*, int64_t, unsigned long long*, hipStream_t);
 template hipError_t launch_count_alive_rec<double>(const Rec<double>*, int64_t, unsigned long long*, hipStream_t);
-template hipError_t launch_append_records<float>(const SpeciesView<float>&, int64_t, const Rec<float>*, const float*,
-                                                 int64_t, int, hipStream_t);
-template hipError_t launch_append_records<double>(const SpeciesView<double>&, int64_t, const Rec<double>*,
-                                                  const double*, int64_t, int, hipStream_t);
+template hipError_t launch_append_records<float>(const AppendArgs<float>&, hipStream_t);
+template hipError_t launch_append_records<double>(const AppendArgs<double>&, hipStream_t);
 template hipError_t launch_eval_rate<float>(const TableView&, int, const float*, const float*, float*, int64_t,
                                             hipStream_t);
 template hipError_t launch_eval_rate<double>(const TableView&, int, const double*, const double*, double*, int64_t,
