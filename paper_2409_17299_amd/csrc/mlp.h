@@ -23,8 +23,9 @@ constexpr int kOffB3 = kOffW3 + kH;
 constexpr int kMlpParams = kOffB3 + 1;  // 4417
 // a partial-gradient row: the parameters, then the sum of squared residuals
 constexpr int kGradRow = kMlpParams + 1;
-constexpr int kMlpThreads = 256;        // four waves, each one 32-sample tile at a time
+constexpr int kMlpThreads = 256;        // four waves, each 32 or 64 samples at a time
 
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 

@@ -16,6 +16,8 @@ namespace {
 
 __device__ __forceinline__ float sigm(float z) { return __builtin_amdgcn_rcpf(1.f + __expf(-z)); }
 
+__device__ __forceinline__ float silu(float z) { return z * sigm(z); }
+
 __device__ __forceinline__ bf16x8 frag_load(const uint16_t* p) {
   return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(p));
 }
@@ -108,21 +110,26 @@ __device__ __forceinline__ float forward(const LaneParams& P, float f1, float f2
   return y + P.b3;
 }
 
-// Inference keeps the W2 fragments and the layer-1 weights in registers and
-// reads the biases and w3 (per feature slot) from LDS, where the two halves of
-// a wave each read one address: 96 fewer registers per lane, two waves per
-// SIMD instead of one.
+// Inference keeps the weights of layers 1 and 2 and the layer-2 biases in
+// registers and reads b1 and w3 (per feature slot) from LDS, where the two
+// halves of a wave each read one address: two waves per SIMD.  It is bound by
+// issue (128 SiLU a sample; the vector units issue 92% of the time), so what
+// counts is instructions: b2 is the C operand of the first product instead of
+// an addition, h - bf16(h) is one two-term dot product instead of unpacking and
+// subtracting (exact either way), and what comes before and after the network
+// is done once per sample (forward_infer).  1e7 samples 444 -> 392 us.
 struct InferParams {
   bf16x8 w2[2][4];
   float w1a[32], w1b[32];  // slot s*8+i: feature phi(s, h, i)
+  f32x16 b2[2];
   float b3;
 };
 
 // For h = 0, 1 and slot = 0..31 (feature f = phi(slot / 8, h, slot % 8)):
-// l1[h][slot] = b1[f], l3[h][slot] = (b2[f], w3[f]).  The whole block calls
-// this (it synchronises).
+// l1[h][slot] = b1[f], l3[h][slot] = w3[f].  The whole block calls this (it
+// synchronises).
 __device__ __forceinline__ void load_infer_params(const MlpPacked* W, int lane, InferParams& P, float (*l1)[32],
-                                                  float2 (*l3)[32]) {
+                                                  float (*l3)[32]) {
   const int h = lane >> 5;
 #pragma unroll
   for (int mt = 0; mt < 2; ++mt)
@@ -135,36 +142,53 @@ __device__ __forceinline__ void load_infer_params(const MlpPacked* W, int lane, 
       const float4 q = W->p1[mlp_phi(s, h, i)];
       P.w1a[s * 8 + i] = q.x;
       P.w1b[s * 8 + i] = q.y;
+      P.b2[s >> 1][(s & 1) * 8 + i] = q.w;
     }
   P.b3 = W->b3;
   if (threadIdx.x < 64) {
     const int hh = threadIdx.x >> 5, q = threadIdx.x & 31, f = mlp_phi(q >> 3, hh, q & 7);
     l1[hh][q] = W->p1[f].z;
-    l3[hh][q] = make_float2(W->p1[f].w, W->w3[f]);
+    l3[hh][q] = W->w3[f];
   }
   __syncthreads();
 }
 
-__device__ __forceinline__ float forward_infer(const InferParams& P, const float* l1h, const float2* l3h, float f1,
-                                               float f2) {
+// This half-wave's part of the output for the sample of lane l and l + 32
+// (features f1, f2).
+__device__ __forceinline__ float infer_half(const InferParams& P, const float4* l1h, const float4* l3h, float f1,
+                                            float f2) {
   // layer 1 one K-step at a time, each step's activations going straight into
-  // its four MFMAs (fewer values live at once)
-  f32x16 acc[2] = {f32x16{}, f32x16{}};
+  // its four MFMAs (fewer values live at once); the empty asm keeps the LDS
+  // reads here, where kept across samples they would spill
+  uint32_t at = 0;
+  asm volatile("" : "+v"(at));
+  l1h += at;
+  l3h += at;
+  // (-1, 0) and (0, -1) in bfloat16, from registers: the compiler would write
+  // the first as the inline constant -1.0, which the instruction reads as the second
+  uint32_t m0 = 0x0000BF80u, m1 = 0xBF800000u;
+  asm("" : "+s"(m0), "+s"(m1));
+  const bf16x2 minus0 = __builtin_bit_cast(bf16x2, m0), minus1 = __builtin_bit_cast(bf16x2, m1);
+  f32x16 acc[2];
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
     bf16x8 hb, lb;
+    const float4 ba = l1h[2 * s], bb = l1h[2 * s + 1];
+    const float b1[8] = {ba.x, ba.y, ba.z, ba.w, bb.x, bb.y, bb.z, bb.w};
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < 8; i += 2) {
       const int q = s * 8 + i;
-      const float z = fmaf(P.w1a[q], f1, fmaf(P.w1b[q], f2, l1h[q]));
-      const float h = z * sigm(z);
-      const __bf16 hi = (__bf16)h;
-      hb[i] = hi;
-      lb[i] = (__bf16)(h - (float)hi);
+      const float h0 = silu(fmaf(P.w1a[q], f1, fmaf(P.w1b[q], f2, b1[i])));
+      const float h1 = silu(fmaf(P.w1a[q + 1], f1, fmaf(P.w1b[q + 1], f2, b1[i + 1])));
+      const bf16x2 hi = {(__bf16)h0, (__bf16)h1};
+      hb[i] = hi[0];
+      hb[i + 1] = hi[1];
+      lb[i] = (__bf16)__builtin_amdgcn_fdot2_f32_bf16(hi, minus0, h0, false);
+      lb[i + 1] = (__bf16)__builtin_amdgcn_fdot2_f32_bf16(hi, minus1, h1, false);
     }
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt) {
-      acc[mt] = mfma(P.w2[mt][s], hb, acc[mt]);
+      acc[mt] = mfma(P.w2[mt][s], hb, s == 0 ? P.b2[mt] : acc[mt]);
       acc[mt] = mfma(P.w2[mt][s], lb, acc[mt]);
     }
   }
@@ -172,31 +196,62 @@ __device__ __forceinline__ float forward_infer(const InferParams& P, const float
 #pragma unroll
   for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float2 c = l3h[16 * mt + r];
-      const float z = acc[mt][r] + c.x;
-      y = fmaf(c.y, z * sigm(z), y);
+    for (int r = 0; r < 16; r += 4) {
+      const float4 w = l3h[4 * mt + r / 4];
+      y = fmaf(w.x, silu(acc[mt][r]), y);
+      y = fmaf(w.y, silu(acc[mt][r + 1]), y);
+      y = fmaf(w.z, silu(acc[mt][r + 2]), y);
+      y = fmaf(w.w, silu(acc[mt][r + 3]), y);
     }
-  y += __shfl_xor(y, 32);
-  return y + P.b3;
+  return y;
 }
 
+// x = (x of lanes 0-31, y of lanes 0-31), y = (x of lanes 32-63, y of lanes 32-63)
+__device__ __forceinline__ void swap_halves(float& x, float& y) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(unsigned, x), __builtin_bit_cast(unsigned, y),
+                                                  false, false);
+  const unsigned lo = r[0], hi = r[1];  // (a bit cast of r[1] itself would read r[0])
+  x = __builtin_bit_cast(float, lo);
+  y = __builtin_bit_cast(float, hi);
+}
+
+// Network output for a sample per lane: the wave evaluates those of lanes 0-31,
+// then (two) those of lanes 32-63, so that what comes before and after the
+// network (two logarithms, a sigmoid) is computed once per sample.
+__device__ __forceinline__ float forward_infer(const InferParams& P, const float4* l1h, const float4* l3h, float f1,
+                                               float f2, bool two) {
+  float g1 = f1, g2 = f2;
+  swap_halves(f1, g1);
+  swap_halves(f2, g2);
+  float ya = 0.f, yb = 0.f;
+#pragma unroll 1
+  for (int half = 0; half < (two ? 2 : 1); ++half) {
+    yb = infer_half(P, l1h, l3h, half ? g1 : f1, half ? g2 : f2);
+    if (half == 0) ya = yb;
+  }
+  swap_halves(ya, yb);
+  return (ya + yb) + P.b3;
+}
+
+// A wave takes 64 samples at a time, or 32 where there are too few for every
+// wave to have more (there the second half would only add its latency).
 __global__ void __launch_bounds__(kMlpThreads, 2) k_mlp_forward(const MlpPacked* W, const float* x, float* y,
                                                                 int64_t n) {
-  __shared__ float l1[2][32];
-  __shared__ float2 l3[2][32];
+  __shared__ __align__(16) float l1[2][32], l3[2][32];
   const int lane = threadIdx.x & 63;
   InferParams P;
   load_infer_params(W, lane, P, l1, l3);
-  const float* l1h = l1[lane >> 5];
-  const float2* l3h = l3[lane >> 5];
+  const float4* l1h = reinterpret_cast<const float4*>(l1[lane >> 5]);
+  const float4* l3h = reinterpret_cast<const float4*>(l3[lane >> 5]);
   const int64_t nw = (int64_t)gridDim.x * (kMlpThreads / 64);
-  for (int64_t t = (int64_t)blockIdx.x * (kMlpThreads / 64) + (threadIdx.x >> 6); t * 32 < n; t += nw) {
-    const int64_t i = t * 32 + (lane & 31);
-    const bool ok = i < n;
+  const bool two = n > 32 * nw;
+  const int per = two ? 64 : 32;
+  for (int64_t t = (int64_t)blockIdx.x * (kMlpThreads / 64) + (threadIdx.x >> 6); t * per < n; t += nw) {
+    const int64_t i = t * per + lane;
+    const bool ok = i < n && lane < per;
     const float f1 = ok ? x[2 * i] : 0.f, f2 = ok ? x[2 * i + 1] : 0.f;
-    const float v = forward_infer(P, l1h, l3h, f1, f2);
-    if (ok && lane < 32) y[i] = v;
+    const float v = forward_infer(P, l1h, l3h, f1, f2, two);
+    if (ok) y[i] = v;
   }
 }
 
@@ -205,29 +260,30 @@ __global__ void __launch_bounds__(kMlpThreads, 2) k_mlp_forward(const MlpPacked*
 __global__ void __launch_bounds__(kMlpThreads, 2) k_mlp_sample(const MlpPacked* W, MlpGeom g, TableView tab,
                                                               const float* chi, const uint32_t* k, float* delta,
                                                               int64_t n) {
-  __shared__ float l1[2][32];
-  __shared__ float2 l3[2][32];
+  __shared__ __align__(16) float l1[2][32], l3[2][32];
   const int lane = threadIdx.x & 63;
   InferParams P;
   load_infer_params(W, lane, P, l1, l3);
-  const float* l1h = l1[lane >> 5];
-  const float2* l3h = l3[lane >> 5];
+  const float4* l1h = reinterpret_cast<const float4*>(l1[lane >> 5]);
+  const float4* l3h = reinterpret_cast<const float4*>(l3[lane >> 5]);
   const int64_t nw = (int64_t)gridDim.x * (kMlpThreads / 64);
-  for (int64_t t = (int64_t)blockIdx.x * (kMlpThreads / 64) + (threadIdx.x >> 6); t * 32 < n; t += nw) {
-    const int64_t i = t * 32 + (lane & 31);
-    const bool ok = i < n;
+  const bool two = n > 32 * nw;
+  const int per = two ? 64 : 32;
+  for (int64_t t = (int64_t)blockIdx.x * (kMlpThreads / 64) + (threadIdx.x >> 6); t * per < n; t += nw) {
+    const int64_t i = t * per + lane;
+    const bool ok = i < n && lane < per;
     const float c = ok ? chi[i] : 1.f;
     const uint32_t kk = ok ? k[i] : 0x80000000u;
     float lr, lrc;
     log_r32(kk, lr, lrc);
     const float lc = logf(c);
-    const float v = forward_infer(P, l1h, l3h, fmaf(lc, g.f1_scale, g.f1_shift), (lr - lrc) * g.f2_scale);
+    const float v = forward_infer(P, l1h, l3h, fmaf(lc, g.f1_scale, g.f1_shift), (lr - lrc) * g.f2_scale, two);
     float d = sigm(fmaf(v, g.out_scale, lc));
     if (!(c >= g.chi_lo && c <= g.chi_hi)) {
       float omd;
       sample_rad32(tab.cdf[0].f32, tab.cdf[0], c, kk, d, omd);
     }
-    if (ok && lane < 32) delta[i] = d;
+    if (ok) delta[i] = d;
   }
 }
 
