@@ -924,21 +924,32 @@ qed_status merge_impl(qed_ensemble* ens, const qed_append* app, hipStream_t st) 
 // monotonically left and reaches the root of the piece that holds it: each
 // step is w <- S(w) / (target - C(w)), with S the weight below w and C the
 // count at or above it; it stops when w no longer decreases.  The passes run
-// on the device (k_level_pass keeps the solve's state there): a few are
-// queued for every species, the host reads the three states once, and queues
-// more only for a solve that has not finished (one pass at a time).  The
-// compactions follow, and their counts are read once at the end.
+// on the device, which keeps the solve's state: all in one launch while the
+// weights fit the chip's LDS (k_level_solve), otherwise a few are queued for
+// every species.  The compactions follow, the host reads the three states once,
+// and queues more passes only for a solve that has not finished (one at a time,
+// and the compactions again).
+// SFQED_LEVEL_WAIT_US: how long a block of the one-launch solve waits for the
+// others before it leaves the rest to the host (default 500; the result is the
+// same).
+uint64_t level_wait_ticks() {
+  const char* v = std::getenv("SFQED_LEVEL_WAIT_US");
+  const long long us = v ? std::atoll(v) : 500;
+  return 100ull * (uint64_t)std::max<long long>(0, std::min<long long>(us, 100000));
+}
+
 template <typename T>
 qed_status resample_impl(qed_ensemble* ens, const qed_resample_cfg* cfg, qed_resample_stats* out, hipStream_t st) {
   Scratch* S = scratch_for_current_device();
   if (!S) return QED_ERR_HIP;
   std::lock_guard<std::mutex> lk(S->mu);
   const size_t part_words = 4 * (size_t)kLevelBlocks;
+  const size_t state_bytes = sizeof(LevelState) * 3 + sizeof(uint64_t) * kSolveSyncWords;
   if (!S->level) {
-    SFQED_HIP(hipMalloc(&S->level, sizeof(double) * 3 * part_words + sizeof(LevelState) * 3));
-    SFQED_HIP(hipMemset(S->level, 0, sizeof(double) * 3 * part_words + sizeof(LevelState) * 3));
+    SFQED_HIP(hipMalloc(&S->level, sizeof(double) * 3 * part_words + state_bytes));
   }
   LevelState* dstate = reinterpret_cast<LevelState*>(S->level + 3 * part_words);
+  unsigned long long* sync = reinterpret_cast<unsigned long long*>(dstate + 3);
   const bool positions = ens->s[0].x != nullptr || ens->s[1].x != nullptr || ens->s[2].x != nullptr;
   qed_resample_stats stats;
   std::memset(&stats, 0, sizeof(stats));
@@ -1003,17 +1014,35 @@ qed_status resample_impl(qed_ensemble* ens, const qed_resample_cfg* cfg, qed_res
     for (int k = 0; k < 3; ++k) {
       la.a[k].state = S->state_c + la.first_block[k];
       la.a[k].epoch = epoch;
-      la.a[k].ticket = reinterpret_cast<unsigned long long*>(S->ctrl + k);
+      la.a[k].ticket = sync + k;
     }
-    SFQED_HIP(hipMemsetAsync(S->ctrl, 0, 8 * sizeof(uint64_t), st));
+    if (forced) SFQED_HIP(hipMemsetAsync(sync, 0, 8 * sizeof(uint64_t), st));
     SFQED_HIP(launch_resample<T>(la, tiles, st));
     return QED_OK;
   };
-  for (int q = 0; q < passes; ++q) SFQED_HIP(launch_level_pass<T>(lv, q == 0 ? 1 : 0, st));
+  SFQED_HIP(hipMemsetAsync(dstate, 0, state_bytes, st));
+  SolveArgs<T> sv;
+  sv.lv = lv;
+  sv.sync = sync;
+  sv.wait = level_wait_ticks();
+  int64_t slots = 0;
+  for (int k = 0; k < 3; ++k) {
+    const int64_t per = (int64_t)kLevelBlocks * kLevelThreads, of_k = (lv.n[k] + per - 1) / per;
+    sv.slots[k] = (int32_t)std::min<int64_t>(of_k, kSolveSlots + 1);
+    slots += of_k;
+  }
+  const bool one_launch = slots <= kSolveSlots && S->num_cu >= kSolveBlocks;
+  if (one_launch) SFQED_HIP(launch_level_solve<T>(sv, st));
+  for (int q = 0; q < passes && !one_launch; ++q) SFQED_HIP(launch_level_pass<T>(lv, q == 0 ? 1 : 0, st));
   if ((rb = compact(0)) != QED_OK) return rb;
   LevelState ls[3];
   if ((rb = read_back(S, ls, dstate, sizeof(ls), st)) != QED_OK) return rb;
   bool late = false;
+  for (int k = 0; k < 3; ++k) late |= lv.solve[k] && !ls[k].started;
+  if (late) {  // not even the first pass: its blocks never were on the chip together
+    SFQED_HIP(launch_level_pass<T>(lv, 1, st));
+    if ((rb = read_back(S, ls, dstate, sizeof(ls), st)) != QED_OK) return rb;
+  }
   // solves that have not finished go on one pass at a time
   while (true) {
     LevelArgs<T> more = lv;

@@ -209,7 +209,7 @@ constexpr int kLevelBlocks = 1024;      // fixed: the sums do not depend on the 
 constexpr uint32_t kResampleJ = 0xFFFFFFFDu;  // Philox counter word of the thinning draw
 constexpr int kLevelDevicePasses = 8;   // threshold passes queued without waiting for the host
 
-// Device state of one species' threshold solve (written by k_level_step, read
+// Device state of one species' threshold solve (written by k_level_step or k_level_solve, read
 // by the next pass and by the host).
 struct LevelState {
   double wt;        // current threshold weight (0: no thinning)
@@ -217,6 +217,7 @@ struct LevelState {
   double total;     // their total weight
   int64_t kept;     // particles after the compaction (written by k_resample)
   int32_t done, iterations;
+  int32_t started, pad;  // the first pass has been made
 };
 
 // One pass of the threshold solves, for the species with solve[k] set.
@@ -229,6 +230,30 @@ struct LevelArgs {
   uint64_t* mask;     // a bit per photon, set by the first pass: it passes the filter
   LevelState* state;  // [3]
   double* part;       // [3][kLevelBlocks][4] the blocks' sums
+};
+
+// The solve in one launch (k_level_solve): 256 blocks of 1024 threads, which
+// hold the weights of the kLevelBlocks x kLevelThreads threads above in LDS, a
+// slot of 4 bytes per particle of a thread.  35 slots and the trees' scratch are
+// 158 of a CU's 160 KiB; species with ceil(n / 262144) slots in all above that
+// (9.2e6 particles) take the two kernels per pass, as do parts of a chip with
+// fewer CUs than blocks.
+constexpr int kSolveThreads = 1024;
+constexpr int kSolveBlocks = kLevelBlocks * kLevelThreads / kSolveThreads;
+constexpr int kSolveGroups = kSolveThreads / kLevelThreads;
+constexpr int kSolveSlots = 35;
+constexpr int kSolvePasses = 32;
+static_assert(kSolveBlocks == 256 && kSolveGroups == 4, "k_level_solve: 16 x 16 blocks, 16 sums a species and block");
+// words of `sync`: the compaction's tickets, the barrier's counters (a line
+// each), eight words per pass; all zero at launch
+constexpr int kSolveCounters = 16, kSolveWords = kSolveCounters + 16 * 17;
+constexpr int kSolveSyncWords = kSolveWords + 8 * kSolvePasses;
+template <typename T>
+struct SolveArgs {
+  LevelArgs<T> lv;
+  unsigned long long* sync;
+  uint64_t wait;     // longest wait at a barrier, in ticks of 10 ns
+  int32_t slots[3];  // per species
 };
 
 template <typename T>
@@ -280,6 +305,8 @@ template <typename T>
 hipError_t launch_merge_photons(const MergeArgs<T>& a, hipStream_t st);
 template <typename T>
 hipError_t launch_level_pass(const LevelArgs<T>& a, int first, hipStream_t st);
+template <typename T>
+hipError_t launch_level_solve(const SolveArgs<T>& a, hipStream_t st);
 template <typename T>
 hipError_t launch_resample(const ResampleLaunch<T>& a, int64_t tiles, hipStream_t st);
 hipError_t launch_count_alive(const uint8_t* alive, int64_t n, unsigned long long* out, hipStream_t st);

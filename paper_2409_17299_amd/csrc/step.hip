@@ -1930,6 +1930,36 @@ __global__ void __launch_bounds__(kLevelThreads) k_level_partials(LevelArgs<T> a
   if (threadIdx.x < 4) a.part[((size_t)k * kLevelBlocks + blockIdx.x) * 4 + threadIdx.x] = sum;
 }
 
+// The solve's next step from the sums v of a pass at threshold wt.
+__device__ __forceinline__ void level_next(const double (&v)[4], bool first, double wt, double target, LevelState& ls) {
+  const double below = v[0], total = v[1], above = v[2], count = v[3];
+  if (first) {
+    ls.eligible = count;
+    ls.total = total;
+    ls.iterations = 0;
+    ls.started = 1;
+    if (target > 0.0 && count > target) {
+      ls.wt = total / target;
+      ls.done = 0;
+    } else {
+      ls.wt = 0.0;
+      ls.done = 1;
+    }
+    return;
+  }
+  ls.iterations += 1;
+  const double room = target - above;
+  if (!(room > 0.0)) {
+    ls.done = 1;
+  } else {
+    const double next = below / room;
+    if (next < wt)
+      ls.wt = next;
+    else
+      ls.done = 1;
+  }
+}
+
 template <typename T>
 __global__ void __launch_bounds__(kLevelThreads) k_level_step(LevelArgs<T> a, int32_t first) {
   __shared__ double red[kLevelThreads][4];
@@ -1937,37 +1967,229 @@ __global__ void __launch_bounds__(kLevelThreads) k_level_step(LevelArgs<T> a, in
   if (!a.solve[k]) return;
   LevelState* ls = a.state + k;
   if (!first && ls->done) return;
-  const double wt = first ? INFINITY : ls->wt, target = (double)a.target[k];
+  const double wt = first ? INFINITY : ls->wt;
   const double* part = a.part + (size_t)k * kLevelBlocks * 4;
   double v[4] = {0.0, 0.0, 0.0, 0.0};
   for (int b = threadIdx.x; b < kLevelBlocks; b += kLevelThreads)
     for (int q = 0; q < 4; ++q) v[q] += part[(size_t)b * 4 + q];
   (void)level_tree(v, red);
   if (threadIdx.x != 0) return;
-  const double below = v[0], total = v[1], above = v[2], count = v[3];
-  if (first) {
-    ls->eligible = count;
-    ls->total = total;
-    ls->iterations = 0;
-    if (target > 0.0 && count > target) {
-      ls->wt = total / target;
-      ls->done = 0;
-    } else {
-      ls->wt = 0.0;
-      ls->done = 1;
+  level_next(v, first != 0, wt, (double)a.target[k], *ls);
+}
+
+// The whole solve in one launch, for ensembles whose weights fit the chip's
+// LDS: a block per CU holds the weights of four of the blocks above, reads
+// them once, and goes through the passes with the others.  Sums, order and steps
+// are those of the two kernels, bit for bit.  A pass ends at a barrier of the
+// grid: the block that arrives last (counters of 16 blocks, then one of the 16)
+// adds the blocks' sums and publishes each species' threshold and status in
+// words of that pass.  Waiting for them is bounded (a.wait): nothing promises
+// that all blocks are on the chip together, so one that has waited too long
+// leaves, and the host goes on from the last pass that was completed, with the
+// two kernels.  State and sums cross the XCDs' L2s: they are written and read
+// with agent-scope atomics only.
+// A pass is a few LDS reads per thread, five trips through memory one after
+// another and two trees, 9 us against 21 of the two launches: 8e6 particles, nine
+// passes, 185 -> 103 us (a fence of the chip's L2s at each barrier made it 185
+// again: hence atomics alone), 3e6 particles 160 -> 82.
+//
+// A pass needs one sum of weights and one count: of all particles in the first,
+// of those below and at or above the threshold in the others.  Counts are exact
+// in any order, so only the weights go through the tree (in the order of
+// level_tree), for the three species together.
+constexpr int kSolveRows = kSolveGroups * (kLevelThreads - 64);  // scratch of the trees, per species
+
+// Sums of 256 threads each, for the species in `live`; the results are in the
+// first wave of each group.
+__device__ __forceinline__ void solve_tree(double (&v)[3], uint32_t live, double* red, int sub, int vt) {
+  const int row = sub * (kLevelThreads - 64) + (vt & 63);
+  for (int k = 0; k < 3; ++k)
+    if (((live >> k) & 1u) && vt >= 64) red[k * kSolveRows + row + (vt & ~63) - 64] = v[k];
+  __syncthreads();
+  if (vt < 64)
+    for (int k = 0; k < 3; ++k)
+      if ((live >> k) & 1u) {
+        const double* m = red + k * kSolveRows + row;
+        v[k] = (v[k] + m[64]) + (m[0] + m[128]);
+        for (int h = 32; h > 0; h >>= 1) v[k] += __shfl_down(v[k], h);  // lanes t < h hold the tree's sums
+      }
+}
+
+template <typename V>
+__device__ __forceinline__ void agent_store(V* at, V v) {
+  __hip_atomic_store(at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The memory operations above are agent-scope atomics, complete for the chip
+// when they have returned.
+__device__ __forceinline__ void await_memory() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kSolveThreads) k_level_solve(SolveArgs<T> a) {
+  extern __shared__ float lds[];
+  __shared__ double s_out[3][kSolveGroups][2];
+  __shared__ int32_t s_count[3][kSolveThreads / 64];
+  __shared__ uint64_t s_word[6];
+  __shared__ int32_t s_last, s_stop;
+  double* red = reinterpret_cast<double*>(lds);
+  float* held = lds + 3 * kSolveRows * 2;  // [slot][thread]
+  const LevelArgs<T>& lv = a.lv;
+  const int tid = threadIdx.x, sub = tid / kLevelThreads, vt = tid % kLevelThreads;
+  const int64_t at = (int64_t)blockIdx.x * kSolveThreads + tid;
+  const int64_t stride = (int64_t)kLevelBlocks * kLevelThreads;
+  constexpr int U = 8;
+  uint64_t in = 0;  // a bit per slot: a particle that passes the filter
+  int slot = 0;
+  for (int k = 0; k < 3; ++k) {
+    if (!lv.solve[k]) continue;
+    const SpeciesView<T>& s = lv.s[k];
+    const int64_t n = lv.n[k];
+    const bool filter = k == 2 && lv.e_min2 > 0.0;
+    for (int u0 = 0; u0 < a.slots[k]; u0 += U) {
+      float w[U];
+      T p[U][3];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t g = at + (u0 + u) * stride, i = g < n ? g : n - 1;
+        w[u] = s.w[i];
+        if (filter) {
+          p[u][0] = s.px[i];
+          p[u][1] = s.py[i];
+          p[u][2] = s.pz[i];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (u0 + u >= a.slots[k]) break;
+        const int64_t g = at + (u0 + u) * stride;
+        bool pass = g < n;
+        if (filter) {
+          pass = pass && passes_filter<T>(p[u], true, lv.e_min2);
+          const uint64_t m = __ballot(pass);
+          if (lane_id() == 0 && g < n) lv.mask[g >> 6] = m;  // for passes after this launch
+        }
+        held[(slot + u0 + u) * kSolveThreads + tid] = w[u];
+        in |= (pass ? 1ull : 0ull) << (slot + u0 + u);
+      }
     }
-    return;
+    slot += a.slots[k];
   }
-  ls->iterations += 1;
-  const double room = target - above;
-  if (!(room > 0.0)) {
-    ls->done = 1;
-  } else {
-    const double next = below / room;
-    if (next < wt)
-      ls->wt = next;
-    else
-      ls->done = 1;
+  double wts[3] = {INFINITY, INFINITY, INFINITY};
+  uint32_t live = 0;  // a bit per species whose solve goes on
+  for (int k = 0; k < 3; ++k) live |= (lv.solve[k] ? 1u : 0u) << k;
+  for (int pass = 0; pass < kSolvePasses; ++pass) {
+    slot = 0;
+    double v[3] = {0.0, 0.0, 0.0};
+    for (int k = 0; k < 3; ++k) {
+      if (!lv.solve[k]) continue;
+      if ((live >> k) & 1u) {
+        const double wt = wts[k];
+        int32_t count = 0;
+#pragma unroll 4
+        for (int u = slot; u < slot + a.slots[k]; ++u) {
+          const double x = held[u * kSolveThreads + tid];
+          const bool pick = (in >> u) & 1ull, below = pick && (pass == 0 || x < wt);
+          if (below) v[k] += x;
+          count += __popcll(__ballot(pass == 0 ? pick : pick && !below));
+        }
+        if ((tid & 63) == 0) s_count[k][tid >> 6] = count;
+      }
+      slot += a.slots[k];
+    }
+    solve_tree(v, live, red, sub, vt);
+    if (vt == 0)
+      for (int k = 0; k < 3; ++k) {
+        const int32_t* c = s_count[k] + sub * (kLevelThreads / 64);
+        s_out[k][sub][0] = v[k];
+        s_out[k][sub][1] = (double)(c[0] + c[1] + c[2] + c[3]);
+      }
+    __syncthreads();
+    if (tid < 64) {
+      const int k = tid >> 3, b = (tid >> 1) & 3, q = tid & 1;
+      if (k < 3 && ((live >> k) & 1u))
+        agent_store(lv.part + ((size_t)k * kLevelBlocks + blockIdx.x * kSolveGroups + b) * 2 + q, s_out[k][b][q]);
+      await_memory();
+      if (tid == 0) {
+        const unsigned long long all = 16ull * pass + 15;
+        unsigned long long* c = a.sync + kSolveCounters + 16 * (blockIdx.x >> 4);
+        bool last = __hip_atomic_fetch_add(c, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == all;
+        if (last) {
+          c = a.sync + kSolveCounters + 16 * 16;
+          last = __hip_atomic_fetch_add(c, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == all;
+        }
+        s_last = last ? 1 : 0;
+      }
+    }
+    __syncthreads();
+    unsigned long long* word = a.sync + kSolveWords + 8 * pass;  // zero: not there yet
+    if (s_last) {
+      // group k: the sums of species k
+      double t[3] = {0.0, 0.0, 0.0}, c = 0.0;
+      const bool mine = (live >> sub) & 1u;
+      if (mine) {
+        double* part = lv.part + (size_t)sub * kLevelBlocks * 2;
+        double p[kLevelBlocks / kLevelThreads][2];
+#pragma unroll
+        for (int b = 0; b < kLevelBlocks / kLevelThreads; ++b)
+          for (int q = 0; q < 2; ++q)
+            p[b][q] = __hip_atomic_load(part + (size_t)(vt + b * kLevelThreads) * 2 + q, __ATOMIC_RELAXED,
+                                        __HIP_MEMORY_SCOPE_AGENT);
+        for (int b = 0; b < kLevelBlocks / kLevelThreads; ++b) {
+          t[0] += p[b][0];
+          c += p[b][1];
+        }
+      }
+      for (int h = 32; h > 0; h >>= 1) c += __shfl_xor(c, h);
+      if ((tid & 63) == 0) s_count[sub < 3 ? sub : 0][sub < 3 ? (vt >> 6) : 15] = (int32_t)c;
+      solve_tree(t, 1u, red, sub, vt);
+      const int32_t* cw = s_count[sub < 3 ? sub : 0];
+      const double count = (double)((int64_t)cw[0] + cw[1] + cw[2] + cw[3]);
+      const double sums[4] = {t[0], t[0], count, count};
+      if (sub < 3 && vt == 0) {
+        LevelState next{};
+        next.wt = sub == 0 ? wts[0] : (sub == 1 ? wts[1] : wts[2]);
+        next.done = 1;
+        if ((live >> sub) & 1u) {
+          next.done = 0;
+          next.iterations = pass - 1;
+          level_next(sums, pass == 0, next.wt, (double)lv.target[sub], next);
+          LevelState* out = lv.state + sub;
+          agent_store(&out->wt, next.wt);
+          if (pass == 0) {
+            agent_store(&out->eligible, next.eligible);
+            agent_store(&out->total, next.total);
+            agent_store(&out->started, 1);
+          }
+          agent_store(&out->done, next.done);
+          agent_store(&out->iterations, next.iterations);
+        }
+        agent_store(word + sub, ~__builtin_bit_cast(unsigned long long, next.wt));
+        agent_store(word + 3 + sub, next.done ? 2ull : 1ull);
+      }
+    }
+    if (tid < 64) {
+      const uint64_t t0 = wall_clock64();
+      unsigned long long got = 1;
+      bool ready;
+      while (true) {
+        if (tid < 6) got = __hip_atomic_load(word + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ready = __all(got != 0);
+        if (ready || wall_clock64() - t0 >= a.wait) break;
+        __builtin_amdgcn_s_sleep(2);
+      }
+      if (tid < 6) s_word[tid] = got;
+      if (tid == 0) s_stop = ready ? 0 : 1;
+    }
+    __syncthreads();
+    if (s_stop) return;
+    for (int k = 0; k < 3; ++k) {
+      wts[k] = __builtin_bit_cast(double, ~s_word[k]);
+      if (s_word[3 + k] == 2) live &= ~(1u << k);
+    }
+    if (!live) return;
+    __syncthreads();  // before the next pass's words
   }
 }
 
@@ -2422,6 +2644,13 @@ hipError_t launch_level_pass(const LevelArgs<T>& a, int first, hipStream_t st) {
 }
 
 template <typename T>
+hipError_t launch_level_solve(const SolveArgs<T>& a, hipStream_t st) {
+  const size_t lds = sizeof(double) * 3 * kSolveRows +
+                     sizeof(float) * kSolveThreads * (size_t)(a.slots[0] + a.slots[1] + a.slots[2]);
+  return launch_step_kernel(&k_level_solve<T>, a, kSolveBlocks, lds, st, kSolveThreads);
+}
+
+template <typename T>
 hipError_t launch_resample(const ResampleLaunch<T>& a, int64_t tiles, hipStream_t st) {
   hipLaunchKernelGGL((k_resample<T>), dim3((unsigned)tiles), dim3(kMergeThreads), 0, st, a);
   return hipGetLastError();
@@ -2507,6 +2736,8 @@ template hipError_t launch_level_pass<float>(const LevelArgs<float>&, int, hipSt
 template hipError_t launch_level_pass<double>(const LevelArgs<double>&, int, hipStream_t);
 template hipError_t launch_count_photon_merged<float>(const StepArgs<float>&, int, size_t, hipStream_t);
 template hipError_t launch_count_photon_merged<double>(const StepArgs<double>&, int, size_t, hipStream_t);
+template hipError_t launch_level_solve<float>(const SolveArgs<float>&, hipStream_t);
+template hipError_t launch_level_solve<double>(const SolveArgs<double>&, hipStream_t);
 template hipError_t launch_resample<float>(const ResampleLaunch<float>&, int64_t, hipStream_t);
 template hipError_t launch_resample<double>(const ResampleLaunch<double>&, int64_t, hipStream_t);
 template hipError_t launch_merge_photons<double>(const MergeArgs<double>&, hipStream_t);
