@@ -24,12 +24,15 @@
 //
 // The build is bound by FP64 arithmetic, nearly all of it in the two Bessel
 // functions: a Newton step of one table entry takes nine of them, and a sum of
-// up to 288 exponentials each time made the default tables 165 ms.  Both are
-// functions of y alone and smooth in ln y once e^-y is taken out, so the sums
-// are taken only at the nodes of piecewise polynomials (k_bessel_table: 688
-// panels, 5,504 sums) and every integrand reads those (16 multiply-adds and an
-// exponential): 165 -> 0.6 ms (k_cdf_rows 109 + 55 -> 0.20 + 0.14, k_rate_nodes
-// 2.0 -> 0.10), the FP32 tables the same and the FP64 ones to 1e-13.
+// up to 288 exponentials each time, by one wave per SIMD, made the default tables
+// 167 ms.  Both are functions of y alone and smooth in ln y once e^-y is taken
+// out, so for the pair tables and the FP32 emission grid the sums are taken only
+// at the nodes of piecewise polynomials (k_bessel_table: 688 panels, 5,504 sums)
+// and every integrand reads those (16 multiply-adds and an exponential): 0.4 ms,
+// FP32 tables the same and the FP64 pair tables to 1e-13.  The FP64 emission
+// tables are held to the last bit, because FP64 records follow from their bits:
+// they are made from the sums, operation by operation, with the work spread over
+// the chip (k_rad_nodes 1.1 ms, k_rad_panels 0.6, k_rad_rows 55 -> 15 ms).
 
 #include <algorithm>
 #include <cmath>
@@ -268,21 +271,16 @@ __device__ double block_sum(double v, double* red) {
   return r;
 }
 
-// Reduced rate integral at chi: emission: int over the whole w line;
-// pairs: twice the half line (scaled by e^{8/(3chi)}).
-template <int P>
-__device__ double reduced_total(const Consts& c, const BesselTable* bt, double chi, double* red) {
-  const Panels pg = panels_for<P>(chi);
+// Reduced pair rate integral at chi: twice the half line (scaled by e^{8/(3chi)}).
+__device__ double pair_total(const Consts& c, const BesselTable* bt, double chi, double* red) {
+  const Panels pg = panels_for<1>(chi);
   double acc = 0.0;
-  for (int k = threadIdx.x; k < npanels<P>(); k += blockDim.x)
-    acc += gl_panel<P>(c, bt, chi, pg.w0 + k * pg.dw, pg.w0 + (k + 1) * pg.dw);
-  double tot = block_sum(acc, red);
-  if (P == 0) tot += integrand<0>(c, bt, chi, kRadW0);  // tail below w0 ~ e^w
-  else tot *= 2.0;
-  return tot;
+  for (int k = threadIdx.x; k < kPairPanels; k += blockDim.x)
+    acc += gl_panel<1>(c, bt, chi, pg.w0 + k * pg.dw, pg.w0 + (k + 1) * pg.dw);
+  return 2.0 * block_sum(acc, red);
 }
 
-__global__ void __launch_bounds__(256) k_rate_nodes(const Consts* cg, const BesselTable* bt, int process, double s_lo,
+__global__ void __launch_bounds__(256) k_pair_nodes(const Consts* cg, const BesselTable* bt, double s_lo,
                                                     double* g_out) {
   __shared__ double red[256];
   const Consts& c = *cg;
@@ -290,11 +288,7 @@ __global__ void __launch_bounds__(256) k_rate_nodes(const Consts* cg, const Bess
   const double xm = cos(kPi * (m + 0.5) / kChebN);
   const double s = s_lo + seg * kChebSegWidth + 0.5 * kChebSegWidth * (xm + 1.0);
   const double chi = exp(s);
-  double tot;
-  if (process == 0)
-    tot = reduced_total<0>(c, bt, chi, red);
-  else
-    tot = reduced_total<1>(c, bt, chi, red);
+  const double tot = pair_total(c, bt, chi, red);
   if (threadIdx.x == 0) g_out[blockIdx.x] = log(tot) - s;  // pairs: + 8/(3chi) is in the scaling
 }
 
@@ -455,6 +449,251 @@ __global__ void __launch_bounds__(kRowThreads) k_cdf_rows(const Consts* cg, cons
   }
 }
 
+// ------------------------------------------------------------------ emission in FP64, from the sums
+// The same operations on each value as bessel_pair, in the same order, by a
+// wave as a whole (all lanes active): the loops run to the longest of its lanes
+// and the constants are scalar loads.
+constexpr double kWaveCut = 70.0;
+__device__ __forceinline__ void bessel_wave(const Consts& c, double y, double y_shift, double& k23, double& ki13) {
+  const bool under = y - y_shift > 745.0, small = !under && y < kYSmall;
+  const bool large = !under && !small && y > 4.0, series = !under && !small && !large;
+  // Terms with y (cosh t - 1) > kWaveCut come first, small terms before large
+  // ones, and are 1e-28 of the sum: they decide no bit of it.
+  int jmax = -1;
+  if (series) {
+    jmax = (int)(acosh(1.0 + kWaveCut / y) * (1.0 / kBesselH)) + 1;
+    jmax = jmax < kBesselN - 1 ? jmax : kBesselN - 1;
+  }
+  int jw = jmax;
+  for (int o = 32; o > 0; o >>= 1) {
+    const int other = __shfl_xor(jw, o);
+    jw = other > jw ? other : jw;
+  }
+  jw = __builtin_amdgcn_readfirstlane(jw);
+  double s23 = 0.0, s13 = 0.0;
+#pragma unroll 2
+  for (int j = jw; j >= 0; --j) {  // small terms first
+    const double a = y * c.bc[j];
+    const double ej = a > kWaveCut ? 0.0 : exp(-a);  // so for all j > jmax
+    s23 = fma(c.b23[j], ej, s23);
+    s13 = fma(c.b13[j], ej, s13);
+  }
+  if (__any(large)) {
+    const double r2y = 1.0 / sqrt(2.0 * y), iy = 1.0 / y;
+    double l23 = 0.0, l13 = 0.0;
+#pragma unroll 1
+    for (int j = kBesselNv - 1; j >= 0; --j) {
+      const double v = j * kBesselHv;
+      const double a = asinh(v * r2y);
+      const double wv = (j == 0 ? 0.5 : 1.0) * kBesselHv * exp(-v * v) * 2.0 * r2y / sqrt(1.0 + v * v * r2y * r2y);
+      const double c23 = cosh(a * (4.0 / 3.0)), c13 = cosh(a * (2.0 / 3.0));
+      l23 = fma(wv, c23, l23);
+      l13 = fma(wv, c13 / (1.0 + v * v * iy), l13);
+    }
+    s23 = large ? l23 : s23;
+    s13 = large ? l13 : s13;
+  }
+  const double e = exp(-(y - y_shift));
+  k23 = s23 * e;
+  ki13 = s13 * e;
+  if (small) {
+    k23 = e * c.k23_small * pow(y, -2.0 / 3.0);
+    ki13 = e * c.ki13_zero;
+  }
+  if (under) {
+    k23 = 0.0;
+    ki13 = 0.0;
+  }
+}
+
+// rad_integrand from the sums
+__device__ __forceinline__ double rad_wave(const Consts& c, double chi, double w) {
+  const double y = exp(3.0 * w);
+  const double z = 1.5 * chi * y;
+  const double omd = 1.0 / (1.0 + z);
+  const double a = omd + (1.0 + z);
+  double k23, ki13;
+  bessel_wave(c, y, 0.0, k23, ki13);
+  return (a * k23 - ki13) * (1.0 / (kSqrt3 * kPi)) * 4.5 * chi * y * omd * omd;
+}
+__device__ __forceinline__ double rad_panel_wave(const Consts& c, double chi, int k) {
+  const double a = kRadW0 + k * kRadDW, b = kRadW0 + (k + 1) * kRadDW;
+  const double m = 0.5 * (a + b), h = 0.5 * (b - a);
+  double s = 0.0;
+#pragma unroll 1
+  for (int i = 0; i < kGL; ++i) s = fma(c.gl_w[i], rad_wave(c, chi, fma(h, c.gl_x[i], m)), s);
+  return s * h;
+}
+
+// Emission rate at the Chebyshev nodes: thread t adds panels t, t + 256, ...
+__global__ void __launch_bounds__(256, 2) k_rad_nodes(const Consts* cg, double s_lo, double* g_out) {
+  __shared__ double red[256];
+  const Consts& c = *cg;
+  const int seg = blockIdx.x / kChebN, m = blockIdx.x % kChebN;
+  const double xm = cos(kPi * (m + 0.5) / kChebN);
+  const double s = s_lo + seg * kChebSegWidth + 0.5 * kChebSegWidth * (xm + 1.0);
+  const double chi = exp(s);
+  double acc = 0.0;
+  for (int k0 = 0; k0 < kRadPanels; k0 += 256) {
+    const int k = k0 + (int)threadIdx.x;
+    const double v = rad_panel_wave(c, chi, k);
+    if (k < kRadPanels) acc += v;
+  }
+  double tot = block_sum(acc, red);
+  tot += rad_wave(c, chi, kRadW0);  // tail below w0 ~ e^w
+  if (threadIdx.x == 0) g_out[blockIdx.x] = log(tot) - s;
+}
+
+// The FP64 grid of emission: chi = exp(s0 + row hs), columns x0 + j hx.
+struct RadGrid {
+  double s0, hs, x0, hx;
+  int rows, cols;
+  double* panels;  // [rows][kRadPanels] panel integrals
+  double* out;
+};
+// One panel of one row per thread.
+__global__ void __launch_bounds__(256, 2) k_rad_panels(const Consts* cg, RadGrid g) {
+  const int n = g.rows * kRadPanels;
+  const int i0 = (int)(blockIdx.x * blockDim.x + threadIdx.x), i = i0 < n ? i0 : n - 1;
+  const double chi = exp(g.s0 + (i / kRadPanels) * g.hs);
+  const double v = rad_panel_wave(*cg, chi, i % kRadPanels);
+  if (i0 < n) g.panels[i] = v;
+}
+
+// Entries of one row: kLanes lanes each (the nodes of the panel rule and the end
+// point), kPerWave of them at a time in a wave (lane 63 follows lane 62), which
+// goes through a contiguous part of the row.  The search is Newton's, with the
+// bracket's middle where a step leaves the bracket.  Once a step has reproduced w
+// to the last bit, w is an end of the bracket, steps that lead back to it are
+// refused, and up to 50 halvings follow; what they end on belongs to the
+// result.  So lanes whose entry is done take the wave's next one, and a halving
+// is decided by the interpolated integrand (1e-13 off, a twentieth of the work)
+// where the sign of G and the step's leaving the bracket hold by ten times that.
+// Bound by the exponentials of the sums: one thread per entry took 55 ms for 277
+// rows of 1057, nine lanes 28 (with the FP32 grid), refilled 21, without the terms
+// that decide nothing 17.5, with the look ahead 15.  Eight blocks a row: with 4
+// their unequal work shows (16.4), with 16 the sums of the panels (19.0 against
+// 17.5).
+constexpr int kLanes = kGL + 1, kPerWave = 64 / kLanes;
+constexpr int kSumThreads = 256;
+constexpr int kSumSplit = 8;
+constexpr double kSumLook = 1e-12;  // the look ahead's margin, of loc / f and of 1
+
+// The sum of the rule over a group's nodes, in their order.
+__device__ __forceinline__ double panel_sum(const Consts& c, double v, int group) {
+  double s = 0.0;
+  for (int i = 0; i < kGL; ++i) s = fma(c.gl_w[i], __shfl(v, group * kLanes + i), s);
+  return s;
+}
+// One step of the search, to wn; false when it has ended.
+__device__ __forceinline__ bool go_on(double wn, double& w, double wlo, double whi, int& it) {
+  const double tol = 1e-15 * fmax(1.0, fabs(w));
+  const bool done = fabs(wn - w) <= tol || whi - wlo <= tol;
+  w = wn;
+  return !done && ++it < 60;
+}
+__global__ void __launch_bounds__(kSumThreads, 4) k_rad_rows(const Consts* cg, const BesselTable* bt, RadGrid g) {
+  const Consts& c = *cg;
+  __shared__ double I[kRadPanels];
+  __shared__ double C[kRadPanels + 1], D[kRadPanels + 1];
+  constexpr int np = kRadPanels;
+  const int row = (int)blockIdx.x, cols = g.cols;
+  const double chi = exp(g.s0 + row * g.hs);
+  for (int k = threadIdx.x; k < np; k += kSumThreads) I[k] = g.panels[(size_t)row * np + k];
+  const double tail = rad_wave(c, chi, kRadW0);
+  __syncthreads();
+  if (threadIdx.x == 0) {  // one addition after another: the two sums in two waves
+    double sum = tail;
+    C[0] = sum;
+    for (int k = 0; k < np; ++k) C[k + 1] = sum = sum + I[k];
+  }
+  if (threadIdx.x == 64) {
+    double sum = 0.0;
+    D[np] = sum;
+    for (int k = np - 1; k >= 0; --k) D[k] = sum = sum + I[k];
+  }
+  __syncthreads();
+  const double total = C[np];
+  const int lane = (int)(threadIdx.x & 63);
+  const int group = (lane < 63 ? lane : 62) / kLanes, part = (lane < 63 ? lane : 62) % kLanes;
+  const double node = c.gl_x[part < kGL ? part : 0];
+  constexpr int waves = kSumSplit * (kSumThreads / 64);
+  const int wave = __builtin_amdgcn_readfirstlane((int)(blockIdx.y * (kSumThreads / 64) + (threadIdx.x >> 6)));
+  int next = cols * wave / waves;
+  const int end = cols * (wave + 1) / waves;
+  int j = end, it = 0;
+  bool busy = false;  // the same in all lanes of a group, as is what follows
+  double a = kRadW0, loc = 0.0, wlo = kRadW0, whi = kRadW0, w = kRadW0;
+  while (true) {
+    const uint64_t idle = __ballot(!busy && part == 0 && lane < 63);
+    if (idle && next < end) {
+      const int mine = next + __popcll(idle & ((1ull << (group * kLanes)) - 1));
+      if (!busy && mine < end) {
+        j = mine;
+        busy = true;
+        it = 0;
+        const double x = g.x0 + j * g.hx;
+        const double r = 1.0 / (1.0 + exp(-x)), rc = 1.0 / (1.0 + exp(x));
+        // find the panel and the integral still to cover inside it, from its left edge
+        int k;
+        if (x <= 0.0) {
+          const double T = r * total;
+          int lo = 0, hi = np;  // C[lo] <= T < C[hi]
+          if (T < C[0]) { lo = 0; hi = 0; }
+          while (hi - lo > 1) {
+            const int mid = (lo + hi) / 2;
+            if (C[mid] <= T) lo = mid; else hi = mid;
+          }
+          k = lo;
+          loc = T - C[k];
+        } else {
+          // from the top: find k with D[k+1] <= T < D[k]
+          const double T = rc * total;
+          int lo = 0, hi = np;  // D[lo] > T >= D[hi]
+          while (hi - lo > 1) {
+            const int mid = (lo + hi) / 2;
+            if (D[mid] > T) lo = mid; else hi = mid;
+          }
+          k = lo;
+          loc = I[k] - (T - D[k + 1]);
+        }
+        k = k < 0 ? 0 : (k >= np ? np - 1 : k);
+        a = kRadW0 + k * kRadDW;
+        const double b = a + kRadDW;
+        wlo = a;
+        whi = b;
+        w = a + (b - a) * fmin(1.0, fmax(0.0, I[k] > 0.0 ? loc / I[k] : 0.5));
+      }
+      next += __popcll(idle);
+    }
+    if (!__any(busy)) break;
+    bool open = busy;
+    while (__any(open)) {  // halvings that the interpolated integrand decides
+      const double m = 0.5 * (a + w), h = 0.5 * (w - a);
+      const double v = rad_integrand(c, bt, chi, part < kGL ? fma(h, node, m) : w);
+      const double G = panel_sum(c, v, group) * h - loc, f = __shfl(v, group * kLanes + kGL);
+      if (!open) continue;
+      const double newton = w - G / f, off = kSumLook * (1.0 + fabs(loc) / f);
+      const double lo = G > 0.0 ? wlo : w, hi = G > 0.0 ? w : whi;
+      open = f > 0.0 && fabs(G) > off * f && (newton < lo - off || newton > hi + off);
+      if (!open) continue;
+      wlo = lo;
+      whi = hi;
+      busy = open = go_on(0.5 * (wlo + whi), w, wlo, whi, it);
+      if (!busy && part == 0) g.out[row * cols + j] = log(1.5) + 3.0 * w;
+    }
+    const double m = 0.5 * (a + w), h = 0.5 * (w - a);  // the rule on [a, w]
+    const double v = rad_wave(c, chi, part < kGL ? fma(h, node, m) : w);
+    const double G = panel_sum(c, v, group) * h - loc, f = __shfl(v, group * kLanes + kGL);
+    if (!busy) continue;
+    if (G > 0.0) whi = w; else wlo = w;
+    double wn = f > 0.0 ? w - G / f : 0.5 * (wlo + whi);
+    if (!(wn > wlo && wn < whi)) wn = 0.5 * (wlo + whi);
+    busy = go_on(wn, w, wlo, whi, it);
+    if (!busy && part == 0) g.out[row * cols + j] = log(1.5) + 3.0 * w;  // logit(delta) - ln chi
+  }
+}
+
 // ------------------------------------------------------------------ host side
 namespace {
 
@@ -553,6 +792,7 @@ qed_status build_tables(const qed_table_cfg& cfg, hipStream_t stream, qed_tables
     o_c32[p] = take(sizeof(float) * g.rows32[p] * g.cols32[p]);
     o_c64[p] = take(sizeof(double) * g.rows64[p] * g.cols64[p]);
   }
+  const size_t o_panels = take(sizeof(double) * g.rows64[0] * kRadPanels);
   t->bytes = off;
   SFQED_HIP(hipMalloc(&t->mem, t->bytes));
   char* base = static_cast<char*>(t->mem);
@@ -579,8 +819,11 @@ qed_status build_tables(const qed_table_cfg& cfg, hipStream_t stream, qed_tables
     double* nodes = reinterpret_cast<double*>(base + o_nodes[p]);
     double* cheb = reinterpret_cast<double*>(base + o_cheb[p]);
     float2* herm = reinterpret_cast<float2*>(base + o_herm[p]);
-    hipLaunchKernelGGL(k_rate_nodes, dim3(g.nseg[p] * kChebN), dim3(256), 0, stream, dconsts, bt, p,
-                       g.cheb_s_lo[p], nodes);
+    if (p == 0)
+      hipLaunchKernelGGL(k_rad_nodes, dim3(g.nseg[p] * kChebN), dim3(256), 0, stream, dconsts, g.cheb_s_lo[p], nodes);
+    else
+      hipLaunchKernelGGL(k_pair_nodes, dim3(g.nseg[p] * kChebN), dim3(256), 0, stream, dconsts, bt, g.cheb_s_lo[p],
+                         nodes);
     hipLaunchKernelGGL(k_cheb_coeffs, dim3(g.nseg[p]), dim3(32), 0, stream, nodes, g.nseg[p], cheb);
     const double hs = g.nseg[p] * kChebSegWidth / (g.herm_n - 1);
     hipLaunchKernelGGL(k_rate_herm, dim3((g.herm_n + 255) / 256), dim3(256), 0, stream, cheb, g.nseg[p],
@@ -599,11 +842,17 @@ qed_status build_tables(const qed_table_cfg& cfg, hipStream_t stream, qed_tables
     const double hs32 = (g.s1[p] - g.s0[p]) / (g.rows32[p] - 1), hx32 = (g.x1[p] - g.x0[p]) / (g.cols32[p] - 1);
     const double hs64 = (g.s1[p] - g.s0[p]) / (g.rows64[p] - 1), hx64 = (g.x1[p] - g.x0[p]) / (g.cols64[p] - 1);
     const GridRows gr{g.s0[p], g.x0[p], hs32, hx32, hs64, hx64, g.rows32[p], g.cols32[p], g.cols64[p], c32, c64};
-    const dim3 rows(g.rows32[p] + g.rows64[p]);
-    if (p == 0)
-      hipLaunchKernelGGL(k_cdf_rows<0>, rows, dim3(kRowThreads), 0, stream, dconsts, bt, gr);
-    else
-      hipLaunchKernelGGL(k_cdf_rows<1>, rows, dim3(kRowThreads), 0, stream, dconsts, bt, gr);
+    if (p == 0) {
+      const RadGrid rg{g.s0[p],     hs64,        g.x0[p], hx64, g.rows64[p], g.cols64[p],
+                       reinterpret_cast<double*>(base + o_panels), c64};
+      const int n = g.rows64[p] * kRadPanels;
+      hipLaunchKernelGGL(k_cdf_rows<0>, dim3(g.rows32[p]), dim3(kRowThreads), 0, stream, dconsts, bt, gr);
+      hipLaunchKernelGGL(k_rad_panels, dim3((n + 255) / 256), dim3(256), 0, stream, dconsts, rg);
+      hipLaunchKernelGGL(k_rad_rows, dim3(g.rows64[p], kSumSplit), dim3(kSumThreads), 0, stream, dconsts, bt, rg);
+    } else {
+      hipLaunchKernelGGL(k_cdf_rows<1>, dim3(g.rows32[p] + g.rows64[p]), dim3(kRowThreads), 0, stream, dconsts, bt,
+                         gr);
+    }
     SFQED_HIP(hipGetLastError());
     CdfView& cv = t->view.cdf[p];
     cv.f32 = c32;
