@@ -82,10 +82,11 @@ constexpr int kStatReplays = 6;         // lepton launches written from the even
 constexpr int kStatReruns = 7;          // lepton launches written by the direct write kernel
 
 // Event log of the lepton count pass, replayed by the write pass
-// (k_replay_lepton in step.hip; format in event_log.h).  Each wave of the
-// count launch writes its own sequence of trip records into blocks handed out
-// from one pool; log_ctl words of the launch: blocks handed out, overflow
-// flag, bytes the launch needed.
+// (k_replay_lepton and k_replay_events in step.hip; format in event_log.h).
+// Each wave of the count launch writes its own sequence of trip records into
+// blocks of one pool, its first block by its own index, further ones handed
+// out; log_ctl words of the launch: blocks handed out beyond the first ones,
+// overflow flag, bytes the launch needed.
 constexpr int kLogUsed = 0, kLogOverflow = 1, kLogNeed = 2;
 // bytes of one lane's slot: an event's z and h in the step's dtype, or a
 // finished particle's optical depth (FP64)

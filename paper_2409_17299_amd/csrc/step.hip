@@ -6,17 +6,18 @@
 // launch is three kernels:
 //   count: every lane runs the sub-cycle loop of one particle, one sub-cycle
 //          per loop trip; a lane whose particle reached the end of the step
-//          takes the next one from a global queue (one atomic per wave), so
+//          takes the next one of its wave's share (WqPlan in step.h), so
 //          lanes stay busy while the event counts of particles differ -- the
 //          role the paper's SortHandledParticles plays for a SIMD chunk
-//          (Sec. 4.3).  It records each particle's event count and writes the
-//          final state of particles without events.
+//          (Sec. 4.3).  It records each particle's event count, writes the
+//          final state of particles without events, and logs the events of
+//          leptons.
 //   scan:  exclusive prefix sum of the counts (single pass, decoupled
 //          look-back between tiles) -> the append offset of every particle's
 //          first child, and the list of particles with events.
-//   write: re-runs the particles with events (same draws, same arithmetic)
-//          and writes their children at the final offsets and their final
-//          state.
+//   write: replays the logged events of leptons, or re-runs the particles
+//          with events (same draws, same arithmetic), and writes their
+//          children at the final offsets and their final state.
 // The append order therefore is: particles in index order, children of one
 // particle in event order -- the same for every run and every grid size.
 
