@@ -396,7 +396,7 @@ qed_status run_launch(Scratch* S, hipStream_t st, const qed_tables* tab, const q
                       const qed_ensemble* ens, qed_append* app, int species, bool from_main, int64_t begin0,
                       int64_t n0, int64_t begin1, int64_t n1, double dt, uint64_t seed, uint32_t step, int* slot,
                       bool positions, EventLog& log, qed_step_stats* stats, bool merged = false,
-                      bool device_n = false) {
+                      bool device_n = false, const AppendArgs<T>* append = nullptr) {
   // part 0: species, particles [begin0, begin0 + n0); part 1 (leptons): species + 1, [begin1, begin1 + n1).
   // device_n (appended photons of a merged step): n0 is only a bound, the
   // range ends where the photon cursor stands when the launch runs; its events
@@ -563,13 +563,19 @@ qed_status run_launch(Scratch* S, hipStream_t st, const qed_tables* tab, const q
   // as many blocks as 512-thread blocks would need, at most one per CU: a
   // small launch still spreads over as many CUs (waves without work leave
   // at once)
-  const int wgrid = photon ? grid : (int)std::min<int64_t>((n + kStepThreads - 1) / kStepThreads, S->num_cu);
+  const int wgrid = (int)std::min<int64_t>((n + kStepThreads - 1) / kStepThreads, S->num_cu);
   // with the event log: the replay (count launch's grid), then the direct
   // write kernel, which returns at once unless the log overflowed
   e = a.log_on ? launch_replay<T>(a, grid, st) : hipSuccess;
-  if (e == hipSuccess)
-    e = photon ? launch_write<T, true>(a, wgrid, lds, st)
-               : launch_write<T, false>(a, wgrid, stage ? stage_off + kLineStageBytes : lds, st, stage);
+  if (photon) {
+    WritePhotonArgs<T> wa;
+    std::memset(&wa, 0, sizeof(wa));
+    wa.step = a;
+    if (append) wa.ap = *append;
+    e = launch_write_photon<T>(wa, grid, lds, st);
+  } else if (e == hipSuccess) {
+    e = launch_write<T>(a, wgrid, stage ? stage_off + kLineStageBytes : lds, st, stage);
+  }
   if (e != hipSuccess) {
     set_error(std::string("write kernel: ") + hipGetErrorString(e));
     return QED_ERR_HIP;
@@ -657,30 +663,29 @@ qed_status step_impl(const qed_tables* tab, const qed_step_cfg* cfg, qed_ensembl
   // The photons appended from g_from on, as far as the round's lepton launch
   // got.  qed_step has read the photon cursor back (cur[0]); the merged
   // step's photon pass reads it on the device (one host wait less per round).
-  auto launch_appended_photons = [&](int64_t g_from) -> qed_status {
+  //
+  // Merged: the records of the round's leptons [from, to) are in their final
+  // state by then, and go after the input leptons beside the photons' writes
+  // (unless they do not fit, which the end reports).
+  auto launch_appended_photons = [&](int64_t g_from, int64_t from, int64_t to) -> qed_status {
     if (!merged) return launch(2, false, g_from, cur[0] - g_from, 0, 0);
-    if (capg - g_from <= 0) return QED_OK;
-    ++launches;
-    return run_launch<T>(S, st, tab, cfg, ens, app, 2, false, g_from, capg - g_from, 0, 0, dt, seed, step, &slot,
-                         positions, log, &local, true, true);
-  };
-  // Merged: the records of leptons [from, to) are in their final state once
-  // their round has run, and go after the input leptons while the round's
-  // read-back is still to come (unless they do not fit, which the end reports).
-  auto append_leptons = [&](int64_t from, int64_t to) -> qed_status {
-    if (!merged || to <= from || ens->s[0].count + to > ens->s[0].capacity ||
-        ens->s[1].count + to > ens->s[1].capacity)
-      return QED_OK;
     AppendArgs<T> ap;
-    for (int s = 0; s < 2; ++s) {
+    std::memset(&ap, 0, sizeof(ap));
+    const bool fits = ens->s[0].count + to <= ens->s[0].capacity && ens->s[1].count + to <= ens->s[1].capacity;
+    for (int s = 0; s < 2 && fits; ++s) {
       ap.dst[s] = view_of<T>(ens->s[s]);
       ap.at[s] = ens->s[s].count + from;
       ap.rec[s] = static_cast<const Rec<T>*>(app[s].rec) + from;
       ap.pos[s] = positions ? static_cast<const T*>(app[s].pos) + 4 * from : nullptr;
       ap.n[s] = to - from;
     }
-    SFQED_HIP(launch_append_records<T>(ap, st));
-    return QED_OK;
+    if (capg - g_from <= 0) {
+      SFQED_HIP(launch_append_records<T>(ap, st));
+      return QED_OK;
+    }
+    ++launches;
+    return run_launch<T>(S, st, tab, cfg, ens, app, 2, false, g_from, capg - g_from, 0, 0, dt, seed, step, &slot,
+                         positions, log, &local, true, true, &ap);
   };
   // after the round's read-back: the appended photons the round processed
   auto photons_done = [&](int64_t g_from) -> int64_t {
@@ -729,7 +734,7 @@ qed_status step_impl(const qed_tables* tab, const qed_step_cfg* cfg, qed_ensembl
       slot += kLaunchWords;
       SFQED_HIP(launch_merge_photons<T>(m, st));
     }
-    if ((rc = launch_appended_photons(0)) != QED_OK) return rc;
+    if ((rc = launch_appended_photons(0, 0, 0)) != QED_OK) return rc;
     if ((rc = read_cursors()) != QED_OK) return rc;
     g_done = photons_done(0);
     overflow = cur[0] > capg || cur[1] > capl;
@@ -746,8 +751,7 @@ qed_status step_impl(const qed_tables* tab, const qed_step_cfg* cfg, qed_ensembl
         break;
       }
     }
-    if ((rc = launch_appended_photons(g_done)) != QED_OK) return rc;
-    if ((rc = append_leptons(l_from, l_hi)) != QED_OK) return rc;
+    if ((rc = launch_appended_photons(g_done, l_from, l_hi)) != QED_OK) return rc;
     if ((rc = read_cursors()) != QED_OK) return rc;
     g_done = photons_done(g_done);
     overflow = cur[0] > capg || cur[1] > capl;

@@ -293,12 +293,25 @@ struct AppendArgs {
   int64_t n[2];
 };
 
+// The photon write pass and, in a merged step, the appending of the round's
+// lepton records (ap.n zero: none).
+template <typename T>
+struct WritePhotonArgs {
+  StepArgs<T> step;
+  AppendArgs<T> ap;
+  int32_t ap_blocks;  // set by the launch
+};
+static_assert(sizeof(WritePhotonArgs<double>) <= 4096, "kernel arguments");
+constexpr int kAppendBlocks = 1024;  // at most, of kStepThreads threads
+
 template <typename T, bool kPhoton>
 hipError_t launch_count(const StepArgs<T>& a, int grid, size_t lds, hipStream_t st);
 template <typename T>
 hipError_t launch_count_photon_merged(const StepArgs<T>& a, int grid, size_t lds, hipStream_t st);
-template <typename T, bool kPhoton>
-hipError_t launch_write(const StepArgs<T>& a, int grid, size_t lds, hipStream_t st, bool stage = false);
+template <typename T>
+hipError_t launch_write_photon(WritePhotonArgs<T>& a, int grid, size_t lds, hipStream_t st);
+template <typename T>
+hipError_t launch_write(const StepArgs<T>& a, int grid, size_t lds, hipStream_t st, bool stage);
 template <typename T>
 hipError_t launch_replay(const StepArgs<T>& a, int grid, hipStream_t st);
 hipError_t launch_scan(const ScanArgs& s, hipStream_t st);
