@@ -31,10 +31,11 @@
  * library-owned device memory that grows (hipMalloc) to the largest launch
  * so far: per-particle counts and offsets, and the event log of the lepton
  * count pass, which the write pass replays.  After a step the log grows to
- * 5/4 of what the step needed, as long as that is at most half of the free
- * device memory; launches whose log does not fit are written by re-running
- * their event loop instead (the same results).  The scratch lives until the
- * process ends.
+ * 5/4 of what the step's waves with events needed (at most 256 KiB for a wave
+ * with few events), as long as that is at most half of the free device memory;
+ * otherwise it stays as it is.  Launches whose log does not fit are written by
+ * re-running their event loop instead (the same results).  The scratch lives
+ * until the process ends.
  *
  * Environment: SFQED_WRITE_STAGING=0 makes the FP32 step store each child
  * record directly instead of staging it in LDS; SFQED_WRITE_REPLAY=0 turns

@@ -31,10 +31,10 @@ constexpr int kCurLepton = kSlots + 1;  // append count of electrons (= positron
 constexpr int kListLen = kSlots + 2;
 constexpr int kMergeCount = kSlots + 3;
 constexpr int kAliveCount = kSlots + 4;
-constexpr int kStats = kSlots + 8;      // 8 words
-constexpr int kResampleCount = kSlots + 16;  // 3 words: survivors of each species' compaction
+constexpr int kStats = kSlots + 8;      // kStatWords words
 constexpr int kMergedCursor = kSlots + 24;   // photons in the main arrays so far (qed_step_merged)
 constexpr int kNonFinite = kSlots + 32;      // 3 words: particles with non-finite values (qed_validate)
+static_assert(kStats + kStatWords <= kMergedCursor, "control words");
 constexpr size_t kPinBytes = 256;            // pinned host bytes for read-backs
 
 // Library-owned scratch of one device: per-particle counts, offsets and event
@@ -67,6 +67,7 @@ struct Scratch {
   uint64_t log_cap = 0;
   uint64_t* log_head = nullptr;
   int64_t log_waves = 0;
+  uint64_t log_own_need = 0;  // the largest pool a launch so far would have needed with a first block for every wave
   // pinned host words for small read-backs (a copy into pageable memory goes
   // through a staging buffer: two copies instead of one)
   int64_t* pin = nullptr;
@@ -234,25 +235,30 @@ qed_status ensure_log_heads(Scratch* s) {
 
 // After a step whose lepton launches needed `need` bytes of event log: grow
 // the pool to 5/4 of that (whole MiB) when it is short, as long as that takes
-// at most half of the free device memory; otherwise launches that need more
-// keep the direct write kernel.  Runs with the stream idle.
-void grow_log(Scratch* s, uint64_t need) {
+// at most half of the free device memory (the old pool counted as free);
+// otherwise the old pool stays, and launches that need more keep the direct
+// write kernel.  Runs with the stream idle.
+void grow_log(Scratch* s, uint64_t need, uint64_t own_need) {
+  s->log_own_need = std::max(s->log_own_need, own_need);
   if (need <= s->log_cap) return;
-  const uint64_t want = ((need + need / 4) + (1ull << 20) - 1) & ~((1ull << 20) - 1);
+  const uint64_t want = ((need + need / 4) + (1ull << 20) - 1) & ~((1ull << 20) - 1), old = s->log_cap;
+  size_t free_b = 0, total_b = 0;
+  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || want > (free_b + old) / 2) return;
   if (s->log_pool) {
     (void)hipDeviceSynchronize();
     (void)hipFree(s->log_pool);
     s->log_pool = nullptr;
     s->log_cap = 0;
   }
-  size_t free_b = 0, total_b = 0;
-  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || want > free_b / 2) return;
-  if (hipMalloc(&s->log_pool, want) != hipSuccess) {
+  for (const uint64_t bytes : {want, old}) {
+    if (!bytes) return;
+    if (hipMalloc(&s->log_pool, bytes) == hipSuccess) {
+      s->log_cap = bytes;
+      return;
+    }
     s->log_pool = nullptr;
     (void)hipGetLastError();
-    return;
   }
-  s->log_cap = want;
 }
 
 // SFQED_WRITE_STAGING=0 makes the lepton write kernel store every child record
@@ -509,6 +515,7 @@ qed_status run_launch(Scratch* S, hipStream_t st, const qed_tables* tab, const q
     grid = g.blocks;
     a.block_waves = g.block_waves;
     a.wq = wq_plan((uint32_t)n, (uint32_t)(g.blocks * g.block_waves));
+    a.log_own = log_own_blocks(a.log_cap, S->log_own_need, a.wq.waves);
   }
 
   ScanArgs s;
@@ -758,7 +765,7 @@ qed_status step_impl(const qed_tables* tab, const qed_step_cfg* cfg, qed_ensembl
     ++rounds;
   }
   const uint64_t* dev_stats = words + (kStats - kCurPhoton);
-  grow_log(S, dev_stats[kStatLogNeed]);  // later steps replay launches this one had to re-run
+  grow_log(S, dev_stats[kStatLogNeed], dev_stats[kStatLogOwn]);  // later steps replay launches this one had to re-run
   local.n_emit = cur[0];
   local.n_pair = cur[1];
   local.n_new[0] = cur[1];

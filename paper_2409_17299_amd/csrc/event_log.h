@@ -40,6 +40,31 @@ constexpr uint64_t kLogJump = 2;
 SFQED_HD constexpr uint64_t log_record_bytes(uint32_t slot) { return kLogHeader + 64ull * slot; }
 SFQED_HD constexpr uint64_t log_records_per_block(uint32_t slot) { return kLogBlock / log_record_bytes(slot); }
 
+// What a wave with `recs` records adds to its launch's tally: the blocks it may
+// take after its first one, and (from bit 40) itself, a wave with records.
+constexpr uint64_t kLogTallyWave = 1ull << 40;
+SFQED_HD constexpr uint64_t log_tally(uint64_t recs, uint32_t slot) {
+  return recs ? kLogTallyWave + recs / (log_records_per_block(slot) - 1) : 0;
+}
+// Pool bytes with which a launch cannot run out, from the sum of its waves'
+// tallies: when every block is handed out on demand (waves without records take
+// nothing, and one block each is spare), and when the first blocks of the pool
+// belong to the launch's `waves` waves, records or not.
+SFQED_HD constexpr uint64_t log_need(uint64_t tally) {
+  return ((tally & (kLogTallyWave - 1)) + 2 * (tally / kLogTallyWave)) * kLogBlock;
+}
+SFQED_HD constexpr uint64_t log_own_need(uint64_t tally, uint32_t waves) {
+  return ((tally & (kLogTallyWave - 1)) + waves) * kLogBlock;
+}
+// Whether a launch's waves own the first blocks of a pool of `cap` bytes, which
+// saves an atomic per wave on one address: only where the pool holds those and
+// the further blocks of every launch seen so far (own_need).  A pool that is
+// smaller hands out all its blocks, so that waves without records take none.  No
+// pool: the pass only measures, and needs no atomics for that.
+SFQED_HD constexpr uint32_t log_own_blocks(uint64_t cap, uint64_t own_need, uint32_t waves) {
+  return cap == 0 || (cap >= own_need && cap >= waves * kLogBlock) ? waves : 0;
+}
+
 // the launch index of fresh lane `lane` of a record
 SFQED_HD inline uint64_t log_fresh_index(uint64_t m_fresh, uint64_t base, int lane) {
   const uint64_t below = lane == 0 ? 0ull : (m_fresh & (~0ull >> (64 - lane)));

@@ -80,14 +80,16 @@ constexpr int kStatBadRoot = 4;         // a record's root named no particle of 
 constexpr int kStatLogNeed = 5;         // largest event log a lepton launch needed (bytes)
 constexpr int kStatReplays = 6;         // lepton launches written from the event log
 constexpr int kStatReruns = 7;          // lepton launches written by the direct write kernel
+constexpr int kStatLogOwn = 8;          // the same as kStatLogNeed with a first block for every wave
+constexpr int kStatWords = 9;
 
 // Event log of the lepton count pass, replayed by the write pass
 // (k_replay_lepton and k_replay_events in step.hip; format in event_log.h).
 // Each wave of the count launch writes its own sequence of trip records into
-// blocks of one pool, its first block by its own index, further ones handed
-// out; log_ctl words of the launch: blocks handed out beyond the first ones,
-// overflow flag, bytes the launch needed.
-constexpr int kLogUsed = 0, kLogOverflow = 1, kLogNeed = 2;
+// blocks of one pool: handed out one by one, or its first block by its own index
+// and further ones handed out (log_own_blocks); log_ctl words of the launch:
+// blocks handed out, overflow flag, the sum of the waves' tallies.
+constexpr int kLogUsed = 0, kLogOverflow = 1, kLogTally = 2;
 // bytes of one lane's slot: an event's z and h in the step's dtype, or a
 // finished particle's optical depth (FP64)
 template <typename T>
@@ -169,8 +171,9 @@ struct StepArgs {
   char* log_pool;                   // log blocks
   uint64_t log_cap;                 // bytes of log_pool (0: the count pass only measures the log)
   uint64_t* log_head;               // per wave of the count launch: 1 + byte offset of its first block, 0 = none
-  unsigned long long* log_ctl;      // the launch's log words (kLogUsed, kLogOverflow, kLogNeed), zero at launch
+  unsigned long long* log_ctl;      // the launch's log words (kLogUsed, kLogOverflow, kLogTally), zero at launch
   int32_t log_on;                   // 1: the count pass logs; the replay writes unless the log overflowed
+  uint32_t log_own;                 // first blocks of the pool that belong to the waves by their index (wq.waves or 0)
   int64_t* offsets_k;               // first-child offset of every particle of the launch (from the scan)
 };
 

@@ -832,9 +832,9 @@ __device__ __forceinline__ void log_trip(const StepArgs<T>& a, LogWriter& w, uin
   if (w.state == 2) return;
   const int lane = lane_id();
   if (w.state == 0 || w.pos + 1 >= kPer) {  // the block's last position is kept for a marker
-    uint32_t b = active;  // its first block is the wave's own; further ones are handed out after all of those
-    if (w.state) {
-      if (lane == 0) b = a.wq.waves + (uint32_t)(atomicAdd(a.log_ctl + kLogUsed, 1ull));
+    uint32_t b = active;  // its first block is the wave's own, if the pool has room for that (log_own_blocks)
+    if (w.state || !a.log_own) {
+      if (lane == 0) b = a.log_own + (uint32_t)(atomicAdd(a.log_ctl + kLogUsed, 1ull));
       b = (uint32_t)__builtin_amdgcn_readfirstlane((int)b);
     }
     const uint64_t blk = (uint64_t)b * kLogBlock;
@@ -861,20 +861,16 @@ __device__ __forceinline__ void log_trip(const StepArgs<T>& a, LogWriter& w, uin
   w.pos += 1;
 }
 
-// Closes the wave's log; returns the blocks of the pool it takes.
+// Closes the wave's log; returns its tally.
 template <typename T>
-__device__ __forceinline__ uint32_t log_close(const StepArgs<T>& a, const LogWriter& w, uint32_t wave) {
+__device__ __forceinline__ uint64_t log_close(const StepArgs<T>& a, const LogWriter& w, uint32_t wave) {
   constexpr uint64_t R = log_record_bytes(log_slot_bytes<T>());
-  constexpr uint64_t kPer = log_records_per_block(log_slot_bytes<T>());
   if (lane_id() == 0) {
     if (w.state == 0) a.log_head[wave] = 0;
     else if (w.state == 1)
       log_header(a.log_pool + (uint64_t)w.blk * kLogBlock + (uint64_t)w.pos * R, 0, 0, 0, kLogEnd);
   }
-  // the blocks this wave's records take (each block keeps its last position
-  // for a marker), plus one for the end marker; without records its first
-  // block is still its own
-  return w.recs ? w.recs / (uint32_t)(kPer - 1) + 2 : 1;
+  return log_tally(w.recs, log_slot_bytes<T>());
 }
 
 // What the waves of a block add to the launch's words when they end, collected
@@ -885,7 +881,8 @@ __device__ __forceinline__ uint32_t log_close(const StepArgs<T>& a, const LogWri
 // largest event count to 1; the host takes that from the number of photons
 // with events).
 struct BlockTotals {
-  uint32_t ended, max_events, log_blocks, capped;
+  uint32_t ended, max_events, capped;
+  unsigned long long log_tally;
 };
 
 // ------------------------------------------------------------------ count kernels
@@ -945,23 +942,21 @@ __global__ void __launch_bounds__(kStepThreads, sizeof(T) == 4 ? kStepWavesPerSi
     local_max = o > local_max ? o : local_max;
   }
   const bool any_capped = __any(capped);
-  uint32_t blocks = 0;
-  if constexpr (kLog) {
-    blocks = log_close<T>(a, lw, wave);
-    if (in_block >= bw) blocks = 0;
-  }
+  uint64_t tally = 0;
+  if constexpr (kLog) tally = log_close<T>(a, lw, wave);
   if (lane_id() == 0) {
     atomicMax(&totals.max_events, (uint32_t)local_max);
-    if (blocks) atomicAdd(&totals.log_blocks, blocks);
+    if (tally) atomicAdd(&totals.log_tally, (unsigned long long)tally);
     if (any_capped) atomicOr(&totals.capped, 1u);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
     if (atomicAdd(&totals.ended, 1u) == kStepThreads / 64 - 1) {
       __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
       volatile BlockTotals* t = &totals;
-      const uint32_t m = t->max_events, c = t->capped, lb = t->log_blocks;
+      const uint32_t m = t->max_events, c = t->capped;
+      const unsigned long long all = t->log_tally;
       if (m) atomicMax(&a.stats[kStatMaxEvents], (unsigned long long)m);
       if (c) atomicOr(&a.stats[kStatCapped], 1ull);
-      if (kLog && lb) atomicAdd(a.log_ctl + kLogNeed, (unsigned long long)lb * kLogBlock);
+      if (kLog && all) atomicAdd(a.log_ctl + kLogTally, all);
     }
   }
 }
@@ -1278,7 +1273,11 @@ template <typename T, bool kMain, bool kStage>
 __global__ void __launch_bounds__(kStage ? kWriteThreads : kStepThreads) k_write_lepton(StepArgs<T> a) {
   constexpr int kThreads = kStage ? kWriteThreads : kStepThreads;
   if (a.log_on) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) atomicMax(&a.stats[kStatLogNeed], a.log_ctl[kLogNeed]);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      const uint64_t tally = a.log_ctl[kLogTally];
+      atomicMax(&a.stats[kStatLogNeed], (unsigned long long)log_need(tally));
+      atomicMax(&a.stats[kStatLogOwn], (unsigned long long)log_own_need(tally, a.wq.waves));
+    }
     if (!a.log_ctl[kLogOverflow]) return;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(&a.stats[kStatReruns], 1ull);
