@@ -41,6 +41,9 @@
  * record directly instead of staging it in LDS; SFQED_WRITE_REPLAY=0 turns
  * the event log off (the write pass re-runs every event loop).  Both give the
  * same results, slower; they exist so that the paths can be compared.
+ * SFQED_LEVEL_WAIT_US (default 500): how long a block of the leveling solve
+ * that runs in one launch waits for the others before the solve goes on pass
+ * by pass (the same results; 0 asks for that).
  *
  * Errors: every function returns a qed_status and never aborts.  Invalid
  * arguments are rejected before any work is queued.
@@ -318,6 +321,8 @@ typedef struct {
   int64_t filtered;        /* photons removed by the energy filter */
   double w_threshold[3];   /* leveling threshold weight; 0 where the species was not thinned */
   int32_t iterations[3];   /* passes of the threshold solve */
+  int16_t one_launch;      /* 1: the solve ran to its end in one launch (else pass by pass, same results) */
+  int16_t read_backs;      /* waits for the stream: 1 unless the passes queued ahead were too few */
 } qed_resample_stats;
 
 void qed_resample_cfg_default(qed_resample_cfg *cfg);  /* no filter, no thinning, seed 0, step 0 */

@@ -96,7 +96,8 @@ class ResampleCfg(C.Structure):
 
 class ResampleStats(C.Structure):
     _fields_ = [("count_before", C.c_int64 * 3), ("count_after", C.c_int64 * 3), ("filtered", C.c_int64),
-                ("w_threshold", C.c_double * 3), ("iterations", C.c_int32 * 3)]
+                ("w_threshold", C.c_double * 3), ("iterations", C.c_int32 * 3),
+                ("one_launch", C.c_int16), ("read_backs", C.c_int16)]
 
     def as_dict(self) -> dict:
         d = {}

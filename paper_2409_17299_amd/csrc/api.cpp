@@ -57,6 +57,7 @@ struct Scratch {
   // solve's count plus one (the solve usually needs the same number from one
   // step to the next), at most kLevelDevicePasses
   int level_passes[3] = {kLevelDevicePasses, kLevelDevicePasses, kLevelDevicePasses};
+  int level_skip = 0;  // leveling solves to come that queue passes, after one in a single launch timed out
   uint64_t* state_m = nullptr;  // look-back words of the merged photon count pass, with their own epochs
   int64_t tiles_m_cap = 0;
   uint32_t epoch_m = 0;
@@ -938,11 +939,16 @@ qed_status merge_impl(qed_ensemble* ens, const qed_append* app, hipStream_t st) 
 // on the device, which keeps the solve's state: all in one launch while the
 // weights fit the chip's LDS (k_level_solve), otherwise a few are queued for
 // every species.  The compactions follow, the host reads the three states once,
-// and queues more passes only for a solve that has not finished (one at a time,
-// and the compactions again).
+// and queues as many passes and the compactions again for a solve that has not
+// finished.
 // SFQED_LEVEL_WAIT_US: how long a block of the one-launch solve waits for the
 // others before it leaves the rest to the host (default 500; the result is the
-// same).
+// same).  Where that happens other work holds a part of the chip, and is likely
+// to hold it for a while: the next kLevelSkip solves on the device queue their
+// passes at once, as the call did before there was a one-launch solve, instead
+// of spending the wait again.  (A wait of 0 is a request for the passes, not a
+// sign of other work.)
+constexpr int kLevelSkip = 16;
 uint64_t level_wait_ticks() {
   const char* v = std::getenv("SFQED_LEVEL_WAIT_US");
   const long long us = v ? std::atoll(v) : 500;
@@ -1042,35 +1048,52 @@ qed_status resample_impl(qed_ensemble* ens, const qed_resample_cfg* cfg, qed_res
     sv.slots[k] = (int32_t)std::min<int64_t>(of_k, kSolveSlots + 1);
     slots += of_k;
   }
-  const bool one_launch = slots <= kSolveSlots && S->num_cu >= kSolveBlocks;
-  if (one_launch) SFQED_HIP(launch_level_solve<T>(sv, st));
-  for (int q = 0; q < passes && !one_launch; ++q) SFQED_HIP(launch_level_pass<T>(lv, q == 0 ? 1 : 0, st));
-  if ((rb = compact(0)) != QED_OK) return rb;
-  LevelState ls[3];
-  if ((rb = read_back(S, ls, dstate, sizeof(ls), st)) != QED_OK) return rb;
-  bool late = false;
-  for (int k = 0; k < 3; ++k) late |= lv.solve[k] && !ls[k].started;
-  if (late) {  // not even the first pass: its blocks never were on the chip together
-    SFQED_HIP(launch_level_pass<T>(lv, 1, st));
-    if ((rb = read_back(S, ls, dstate, sizeof(ls), st)) != QED_OK) return rb;
+  bool one_launch = slots <= kSolveSlots && S->num_cu >= kSolveBlocks;
+  if (one_launch && S->level_skip > 0) {
+    --S->level_skip;
+    one_launch = false;
   }
-  // solves that have not finished go on one pass at a time
+  auto queue_passes = [&](const LevelArgs<T>& a, bool first, int count) -> qed_status {
+    for (int q = 0; q < count; ++q) SFQED_HIP(launch_level_pass<T>(a, first && q == 0 ? 1 : 0, st));
+    return QED_OK;
+  };
+  LevelState ls[3];
+  auto read_states = [&]() -> qed_status {
+    ++stats.read_backs;
+    return read_back(S, ls, dstate, sizeof(ls), st);
+  };
+  if (one_launch) SFQED_HIP(launch_level_solve<T>(sv, st));
+  else if ((rb = queue_passes(lv, true, passes)) != QED_OK) return rb;
+  if ((rb = compact(0)) != QED_OK) return rb;
+  if ((rb = read_states()) != QED_OK) return rb;
+  bool in_one = one_launch, timed_out = false;
+  // solves that have not finished (all of them have made the same passes)
   while (true) {
     LevelArgs<T> more = lv;
-    bool any = false;
+    bool any = false, none_yet = false;
+    int made = 0;
     for (int k = 0; k < 3; ++k) {
-      more.solve[k] = lv.solve[k] && !ls[k].done && ls[k].iterations < 100;
-      any |= more.solve[k] != 0;
+      more.solve[k] = lv.solve[k] && !ls[k].done && ls[k].iterations < kLevelMaxPasses;
+      if (!more.solve[k]) continue;
+      any = true;
+      none_yet |= !ls[k].started;  // not even the first pass: its blocks never were on the chip together
+      made = std::max(made, ls[k].iterations);
     }
     if (!any) break;
-    late = true;
-    SFQED_HIP(launch_level_pass<T>(more, 0, st));
-    if ((rb = read_back(S, ls, dstate, sizeof(ls), st)) != QED_OK) return rb;
+    timed_out |= in_one && (none_yet || made + 1 < kSolvePasses);
+    in_one = false;
+    const int count = none_yet ? passes : std::max(1, std::min(passes - 1, kLevelMaxPasses - made));
+    if ((rb = queue_passes(more, none_yet, count)) != QED_OK) return rb;
+    if ((rb = compact(0)) != QED_OK) return rb;
+    if ((rb = read_states()) != QED_OK) return rb;
   }
-  for (int k = 0; k < 3; ++k) late |= lv.solve[k] && !ls[k].done;  // stopped at the limit of passes
-  if (late) {
+  stats.one_launch = in_one ? 1 : 0;
+  if (timed_out && sv.wait > 0) S->level_skip = kLevelSkip;
+  bool stopped = false;
+  for (int k = 0; k < 3; ++k) stopped |= lv.solve[k] && !ls[k].done;
+  if (stopped) {  // at the limit of passes: with the thresholds reached
     if ((rb = compact(1)) != QED_OK) return rb;
-    if ((rb = read_back(S, ls, dstate, sizeof(ls), st)) != QED_OK) return rb;
+    if ((rb = read_states()) != QED_OK) return rb;
   }
   for (int k = 0; k < 3; ++k)
     if (lv.solve[k] && cfg->target[k] > 0)

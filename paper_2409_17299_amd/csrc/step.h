@@ -212,6 +212,7 @@ constexpr int kLevelThreads = 256;
 constexpr int kLevelBlocks = 1024;      // fixed: the sums do not depend on the size of the launch
 constexpr uint32_t kResampleJ = 0xFFFFFFFDu;  // Philox counter word of the thinning draw
 constexpr int kLevelDevicePasses = 8;   // threshold passes queued without waiting for the host
+constexpr int kLevelMaxPasses = 100;    // a solve stops there
 
 // Device state of one species' threshold solve (written by k_level_step or k_level_solve, read
 // by the next pass and by the host).
@@ -248,9 +249,9 @@ constexpr int kSolveGroups = kSolveThreads / kLevelThreads;
 constexpr int kSolveSlots = 35;
 constexpr int kSolvePasses = 32;
 static_assert(kSolveBlocks == 256 && kSolveGroups == 4, "k_level_solve: 16 x 16 blocks, 16 sums a species and block");
-// words of `sync`: the compaction's tickets, the barrier's counters (a line
-// each), eight words per pass; all zero at launch
-constexpr int kSolveCounters = 16, kSolveWords = kSolveCounters + 16 * 17;
+// words of `sync`: the compaction's tickets, whether a block has left, the
+// barrier's counters (a line each), eight words per pass; all zero at launch
+constexpr int kSolveLeft = 8, kSolveCounters = 16, kSolveWords = kSolveCounters + 16 * 17;
 constexpr int kSolveSyncWords = kSolveWords + 8 * kSolvePasses;
 template <typename T>
 struct SolveArgs {

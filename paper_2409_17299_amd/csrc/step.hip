@@ -2025,8 +2025,8 @@ __global__ void __launch_bounds__(kLevelThreads) k_level_step(LevelArgs<T> a, in
 // adds the blocks' sums and publishes each species' threshold and status in
 // words of that pass.  Waiting for them is bounded (a.wait): nothing promises
 // that all blocks are on the chip together, so one that has waited too long
-// leaves, and the host goes on from the last pass that was completed, with the
-// two kernels.  State and sums cross the XCDs' L2s: they are written and read
+// leaves and says so, the others follow without waiting in turn, and the host
+// goes on from the last pass that was completed, with the two kernels.  State and sums cross the XCDs' L2s: they are written and read
 // with agent-scope atomics only.
 // A pass is a few LDS reads per thread, five trips through memory one after
 // another and two trees, 9 us against 21 of the two launches: 8e6 particles, nine
@@ -2211,16 +2211,21 @@ __global__ void __launch_bounds__(kSolveThreads) k_level_solve(SolveArgs<T> a) {
     }
     if (tid < 64) {
       const uint64_t t0 = wall_clock64();
-      unsigned long long got = 1;
-      bool ready;
+      const unsigned long long* poll = tid < 6 ? word + tid : a.sync + kSolveLeft;
+      unsigned long long got = 0;
+      bool ready, left;
       while (true) {
-        if (tid < 6) got = __hip_atomic_load(word + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        ready = __all(got != 0);
-        if (ready || wall_clock64() - t0 >= a.wait) break;
+        if (tid < 7) got = __hip_atomic_load(poll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        ready = __all(tid >= 6 || got != 0);
+        left = __any(tid == 6 && got != 0);
+        if (ready || left || wall_clock64() - t0 >= a.wait) break;
         __builtin_amdgcn_s_sleep(2);
       }
       if (tid < 6) s_word[tid] = got;
-      if (tid == 0) s_stop = ready ? 0 : 1;
+      if (tid == 0) {
+        s_stop = ready ? 0 : 1;
+        if (!ready && !left) agent_store(a.sync + kSolveLeft, 1ull);
+      }
     }
     __syncthreads();
     if (s_stop) return;
