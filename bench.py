@@ -69,6 +69,14 @@ def kernel_bytes(name: str, st: dict, n_main: list, n_step: int, merged: bool = 
     raise KeyError(name)
 
 
+def group_bytes(name: str, st: dict, n_main: list, n_step: int, merged: bool = True, push: bool = False) -> float:
+    """kernel_bytes plus what the group's launches do besides: in a merged step
+    the photon write launches also append the lepton records to the main arrays
+    (a 48-byte record read; p 12, w 4, tau 8, id 8 written)."""
+    b = kernel_bytes(name, st, n_main, n_step, merged=merged, push=push)
+    return b + 2 * st["n_pair"] * (48 + 32) if merged and name == "write_photon" else b
+
+
 # ----------------------------------------------------------------------------- measured HBM traffic
 def measured_traffic(kernel: str):
     """HBM bytes per launch of the kernel group `kernel` from the committed
@@ -363,7 +371,7 @@ def cascade_leg(sf, torch, n_seeds: int = 1_000_000, steps: int = 20) -> dict:
     kern = {}
     for k, name in enumerate(sf.StepStats.KERNELS):
         if S["kernel_launches"][k]:
-            b = kernel_bytes(name, S, n_main, 1, merged=True, push=True)
+            b = group_bytes(name, S, n_main, 1, merged=True, push=True)
             kern[name] = {"ms_total": round(S["kernel_ms"][k], 4), "launches": S["kernel_launches"][k],
                           "gbs": round(b / (S["kernel_ms"][k] * 1e-3) / 1e9, 1)}
     dom = max(kern, key=lambda k: kern[k]["ms_total"])
@@ -747,7 +755,7 @@ def main(argv=None):
     for k, name in enumerate(sf.StepStats.KERNELS):
         if S["kernel_launches"][k] == 0:
             continue
-        b = kernel_bytes(name, S, dw.n, args.steps, merged=not args.two_call)
+        b = group_bytes(name, S, dw.n, args.steps, merged=not args.two_call)
         kern[name] = {"ms_total": S["kernel_ms"][k], "launches": S["kernel_launches"][k],
                       "avg_launch_ms": S["kernel_ms"][k] / S["kernel_launches"][k],
                       "bytes": b, "gbs": b / (S["kernel_ms"][k] * 1e-3) / 1e9}

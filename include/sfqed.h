@@ -218,7 +218,8 @@ typedef struct {
   int64_t required_capacity[3];     /* append sizes needed (lower bound on overflow) */
   int64_t n_launches;               /* particle-range launches (count, scan, write each) */
   /* Per kernel, indexed 0 count (leptons), 1 scan, 2 write (leptons),
-   * 3 count (photons), 4 write (photons).  kernel_ms needs profile = 1 (HIP
+   * 3 count (photons), 4 write (photons; in a merged step also the appending
+   * of the round's lepton records to the main arrays).  kernel_ms needs profile = 1 (HIP
    * events on the step's stream, read after the step; no extra waits). */
   double kernel_ms[5];
   int64_t kernel_launches[5];
