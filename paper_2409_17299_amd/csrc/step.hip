@@ -1399,21 +1399,24 @@ __device__ __forceinline__ void replay_event(const StepArgs<T>& a, Lane<T>& L, T
 // child offset plus the event index, and a lane whose particle finished moves
 // it to the end of the step and stores its final state with the logged
 // optical depth.  No tables are needed, so LDS holds only the source table
-// and a whole 128-byte line per lane for the child records, written out by
-// eight lanes per line.  Large FP32 launches only (see k_replay_events).
+// and (FP32) a whole 128-byte line per lane for the child records, written
+// out by eight lanes per line.  Large launches (see k_replay_events).
 constexpr int kReplayLine = 8;
 template <typename T, bool kMain, bool kPush, bool kPos>
-__global__ void __launch_bounds__(kStepThreads, kStepWavesPerSimd) k_replay_lepton(StepArgs<T> a) {
+__global__ void __launch_bounds__(kStepThreads, sizeof(T) == 4 ? kStepWavesPerSimd : 1) k_replay_lepton(StepArgs<T> a) {
+  constexpr bool kStage = sizeof(T) == 4;
   if (!a.log_on || a.log_ctl[kLogOverflow]) return;  // the direct write kernel does the writes
   if (blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(&a.stats[kStatReplays], 1ull);
   extern __shared__ float lds[];
-  __shared__ uint8_t owners[kStepThreads / 64][64];
+  __shared__ uint8_t owners[kStage ? kStepThreads / 64 : 1][64];
   SrcTable* src = reinterpret_cast<SrcTable*>(lds);
   stage_sources<T>(a, src);
   __syncthreads();
   constexpr int kSlot = kReplayLine + 1;
-  uint4* wave_slots = reinterpret_cast<uint4*>(reinterpret_cast<char*>(lds) + sizeof(SrcTable)) +
-                      (threadIdx.x & ~63u) * kSlot;
+  uint4* wave_slots = nullptr;
+  if constexpr (kStage)
+    wave_slots = reinterpret_cast<uint4*>(reinterpret_cast<char*>(lds) + sizeof(SrcTable)) +
+                 (threadIdx.x & ~63u) * kSlot;
   const uint32_t wave = blockIdx.x * (kStepThreads / 64) + (threadIdx.x >> 6);
   const uint64_t head = a.log_head[wave];
   if (head == 0) return;
@@ -1469,7 +1472,14 @@ __global__ void __launch_bounds__(kStepThreads, kStepWavesPerSimd) k_replay_lept
       have = true;
     }
     if (ev) {
-      const T z = __builtin_bit_cast(float, sl.x), h = __builtin_bit_cast(float, sl.y);
+      T z, h;
+      if constexpr (sizeof(T) == 4) {
+        z = __builtin_bit_cast(float, sl.x);
+        h = __builtin_bit_cast(float, sl.y);
+      } else {
+        z = __builtin_bit_cast(double, join64(sl.x, sl.y));
+        h = __builtin_bit_cast(double, join64(sl.z, sl.w));
+      }
       replay_event<T, kPush, kPos>(a, L, q, z, h, obase, O);
     } else if (fin) {
       const double tf = __builtin_bit_cast(double, join64(sl.x, sl.y));
@@ -1480,19 +1490,21 @@ __global__ void __launch_bounds__(kStepThreads, kStepWavesPerSimd) k_replay_lept
       L.tau = tf;
       stage_final<T>(a, L, true, false, true, O);
     }
-    if (O.what & kOutChild) {
-      stage_child<kReplayLine, T>(wave_slots + lane * kSlot, cl, a.out_rec[0], O.at, O.r);
-      if constexpr (kPos) {
-        T* qp = a.out_pos[0] + 4 * O.at;
-        qp[0] = O.x[0];
-        qp[1] = O.x[1];
-        qp[2] = O.x[2];
-        qp[3] = T(0);
+    if constexpr (kStage) {
+      if (O.what & kOutChild) {
+        stage_child<kReplayLine, T>(wave_slots + lane * kSlot, cl, a.out_rec[0], O.at, O.r);
+        if constexpr (kPos) {
+          T* qp = a.out_pos[0] + 4 * O.at;
+          qp[0] = O.x[0];
+          qp[1] = O.x[1];
+          qp[2] = O.x[2];
+          qp[3] = T(0);
+        }
+        O.what &= ~kOutChild;
       }
-      O.what &= ~kOutChild;
     }
     flush<T>(a, src, O);
-    line_flush<kReplayLine, T>(wave_slots, owners[threadIdx.x >> 6], cl, fin);
+    if constexpr (kStage) line_flush<kReplayLine, T>(wave_slots, owners[threadIdx.x >> 6], cl, fin);
     if (fin) have = false;
     h0 = h0_n;
     h1 = h1_n;
@@ -1517,14 +1529,10 @@ __global__ void __launch_bounds__(kStepThreads, kStepWavesPerSimd) k_replay_lept
 //      takes kTrips trips of 64 / kTrips lanes, so the children of one parent
 //      are stored next to each other.
 // Write pass of 1e3 crossed-field particles 367 -> 125 us (all rounds), of 1e5
-// electrons in a static field 130 -> 79 us.  FP32 launches with more than one
-// wave per SIMD keep k_replay_lepton: the chains hide one another, its records
-// leave in whole lines, and here three waves of a block wait for the second
-// phase and LDS holds four blocks per CU (4e6 particles: 5.5 ms there, 6.2 ms
-// here; 1e6 leptons with one event each: 40 against 56 us).  In FP64, where
-// that kernel stored its records piece by piece, this one is the faster at every
-// size (the step of 2e5 particles 4.78 against 4.62 ms, of 1.5e6 19.06 against
-// 18.21).
+// electrons in a static field 130 -> 79 us.  It pays while there is little else to
+// hide a chain: three waves of a block wait for the second phase, and a tile
+// of FP64 with push and positions leaves two blocks per CU.  Which launches are
+// replayed by lanes instead, launch_replay_as says, with both sides' times.
 constexpr int kReplayThreads = 256, kReplayWaves = kReplayThreads / 64;
 constexpr uint32_t kEntryEvent = 0x40000000u, kEntryFinal = 0x80000000u;
 
@@ -2635,15 +2643,27 @@ hipError_t launch_write(const StepArgs<T>& a, int grid, size_t lds, hipStream_t 
   return launch_step_kernel(&k_write_lepton<T, false, false>, a, grid, lds, st);
 }
 // The replay by lanes runs the count launch's grid, the replay by events one
-// block per wave of it.  By events: FP64, and FP32 launches with one wave per
-// SIMD (measured beside k_replay_events).
+// block per wave of it.
+// FP32: by events up to one wave per SIMD.  Electrons in a static field, by lanes
+// against by events, in us: 3e4 with 95 events each 224 / 114, 2e5 with 25 events
+// 226 / 201, with one 34 / 34; above, 1.1e6 with 12 events 334 / 361, with one
+// 55 / 62, 4e6 with one 178 / 244.
+// FP64: by events up to a log per CU (16,384 particles; 1.6e4 with 95 events 208 /
+// 125, with push and positions 247 / 185).  Then the chains hide one another, the
+// more so the larger the tile: 6.4e4 with 25 events 92 / 114, with push 102 / 201,
+// with positions 108 / 163, both 113 / 242; 1.1e6 with one event and push 89 / 165,
+// 4e6 336 / 532.  Without either, where the tile is small, launches of more
+// than one wave per SIMD go by events again for what that saves where there are
+// many: 4e5 with 25 events 550 / 406, 1.1e6 with 12 706 / 523 (with one 72 / 82).
+constexpr uint32_t kReplayLogs = 256;
 template <typename T, bool kMain, bool kPush, bool kPos>
 hipError_t launch_replay_as(const StepArgs<T>& a, int grid, hipStream_t st) {
-  if constexpr (sizeof(T) == 4) {
-    if (a.block_waves == kStepThreads / 64)
-      return launch_step_kernel(&k_replay_lepton<T, kMain, kPush, kPos>, a, grid,
-                                sizeof(SrcTable) + (size_t)kStepThreads * (kReplayLine + 1) * 16, st);
-  }
+  const bool full_simds = a.block_waves == kStepThreads / 64;
+  const bool lanes =
+      sizeof(T) == 4 ? full_simds : a.wq.waves > kReplayLogs && (kPush || kPos || !full_simds);
+  if (lanes)
+    return launch_step_kernel(&k_replay_lepton<T, kMain, kPush, kPos>, a, grid,
+                              sizeof(SrcTable) + (sizeof(T) == 4 ? kStepThreads * (kReplayLine + 1) * 16 : 0), st);
   return launch_step_kernel(&k_replay_events<T, kMain, kPush, kPos>, a, grid * (kStepThreads / 64),
                             sizeof(SrcTable) + ReplayTile<T, kMain, kPush, kPos>::kBytes, st, kReplayThreads);
 }

@@ -1,8 +1,9 @@
-"""The replay by lanes (FP32 launches of more than 256 leptons per SIMD) against
-the direct write kernel, over the forms it is compiled for: push and positions
-on and off, sources in the ensemble and in records, with and without the
-counters of launches above 512 particles per wave.  Records, positions, final
-states and counts must be the same bits."""
+"""The replay of large launches (more than 256 leptons per SIMD) against the
+direct write kernel, over the forms it is compiled for: by lanes in FP32 and in
+FP64 with push or positions, by events in FP64 without either, sources in the
+ensemble and in records, with and without the counters of launches above 512
+particles per wave.  Records, positions, final states and counts must be the
+same bits."""
 import numpy as np
 import pytest
 
@@ -16,10 +17,11 @@ BY_LANES = 256 * 4 * 256  # leptons of a launch on 256 CUs, above which it is re
 
 @pytest.mark.parametrize("push", [False, True])
 @pytest.mark.parametrize("positions", [False, True])
+@pytest.mark.parametrize("dtype_name", ["float32", "float64"])
 @pytest.mark.parametrize("n", [132_001, 1_060_003])  # of each species
-def test_equals_direct_writes(monkeypatch, push, positions, n):
+def test_equals_direct_writes(monkeypatch, dtype_name, push, positions, n):
     torch, sf = need_gpu()
-    dtype = torch.float32
+    dtype = getattr(torch, dtype_name)
     photons = max(n, 300_000)
     wl = synth.crossed_field(10_000_000, indices=[np.arange(n), np.arange(n) + 5, np.arange(photons)])
     wl.species[2].tau[:] *= 1e-6  # nearly every photon makes a pair at once: the next round's leptons are records
