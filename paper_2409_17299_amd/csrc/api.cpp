@@ -976,6 +976,7 @@ qed_status resample_impl(qed_ensemble* ens, const qed_resample_cfg* cfg, qed_res
   lv.e_min2 = e_min2;
   lv.state = dstate;
   lv.part = S->level;
+  lv.tickets = sync;
   int passes = 0;
   for (int k = 0; k < 3; ++k) {
     const int64_t n = ens->s[k].count;
@@ -1037,7 +1038,6 @@ qed_status resample_impl(qed_ensemble* ens, const qed_resample_cfg* cfg, qed_res
     SFQED_HIP(launch_resample<T>(la, tiles, st));
     return QED_OK;
   };
-  SFQED_HIP(hipMemsetAsync(dstate, 0, state_bytes, st));
   SolveArgs<T> sv;
   sv.lv = lv;
   sv.sync = sync;
@@ -1048,7 +1048,8 @@ qed_status resample_impl(qed_ensemble* ens, const qed_resample_cfg* cfg, qed_res
     sv.slots[k] = (int32_t)std::min<int64_t>(of_k, kSolveSlots + 1);
     slots += of_k;
   }
-  bool one_launch = slots <= kSolveSlots && S->num_cu >= kSolveBlocks;
+  // (a filter without targets is one pass, without a barrier to save)
+  bool one_launch = passes > 1 && slots <= kSolveSlots && S->num_cu >= kSolveBlocks;
   if (one_launch && S->level_skip > 0) {
     --S->level_skip;
     one_launch = false;
@@ -1062,8 +1063,10 @@ qed_status resample_impl(qed_ensemble* ens, const qed_resample_cfg* cfg, qed_res
     ++stats.read_backs;
     return read_back(S, ls, dstate, sizeof(ls), st);
   };
-  if (one_launch) SFQED_HIP(launch_level_solve<T>(sv, st));
-  else if ((rb = queue_passes(lv, true, passes)) != QED_OK) return rb;
+  if (one_launch) {
+    SFQED_HIP(hipMemsetAsync(dstate, 0, state_bytes, st));
+    SFQED_HIP(launch_level_solve<T>(sv, st));
+  } else if ((rb = queue_passes(lv, true, passes)) != QED_OK) return rb;
   if ((rb = compact(0)) != QED_OK) return rb;
   if ((rb = read_states()) != QED_OK) return rb;
   bool in_one = one_launch, timed_out = false;

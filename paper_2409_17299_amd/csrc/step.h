@@ -235,6 +235,7 @@ struct LevelArgs {
   uint64_t* mask;     // a bit per photon, set by the first pass: it passes the filter
   LevelState* state;  // [3]
   double* part;       // [3][kLevelBlocks][4] the blocks' sums
+  unsigned long long* tickets;  // [3] of the compaction that follows, cleared by the first pass
 };
 
 // The solve in one launch (k_level_solve): 256 blocks of 1024 threads, which

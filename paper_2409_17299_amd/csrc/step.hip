@@ -2032,6 +2032,7 @@ __global__ void __launch_bounds__(kLevelThreads) k_level_step(LevelArgs<T> a, in
     for (int q = 0; q < 4; ++q) v[q] += part[(size_t)b * 4 + q];
   (void)level_tree(v, red);
   if (threadIdx.x != 0) return;
+  if (first) a.tickets[k] = 0;
   level_next(v, first != 0, wt, (double)a.target[k], *ls);
 }
 

@@ -87,3 +87,14 @@ def test_more_passes_than_the_launch_makes(monkeypatch):
     assert a[1].read_backs == 1 + (a[1].iterations[0] - 31 + 7) // 8
     assert b[1].read_backs == 2 + (b[1].iterations[0] - 8 + 7) // 8
     same(torch, a, b)
+
+
+def test_filter_alone_is_one_pass():
+    torch, sf = need_gpu()
+    n = (300, 5000, 70_001)
+    for _ in range(2):
+        main, st = base.resample(sf, torch, n, torch.float32, photon_energy_min=2.0)
+        assert st.one_launch == 0 and st.read_backs == 1
+        assert list(st.count_after[:2]) == [300, 5000] and st.filtered == n[2] - main[2].count > 0
+        main, st = base.resample(sf, torch, n, torch.float32, photon_energy_min=1e-6)
+        assert st.read_backs == 1 and st.filtered == 0 and list(st.count_after) == list(n)
