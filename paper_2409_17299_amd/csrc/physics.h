@@ -237,7 +237,7 @@ __device__ __forceinline__ T row_interp(const P* row, int cols, T ux) {
   return w[0] * (T)row[j - 1] + w[1] * (T)row[j] + w[2] * (T)row[j + 1] + w[3] * (T)row[j + 2];
 }
 
-template <typename T, typename P>
+template <typename T, typename P, bool kTogether = true>
 __device__ __forceinline__ T grid_interp(const P* tab, int rows, int cols, T us, T ux) {
   int i = (int)floor(us);
   i = i < 1 ? 1 : (i > rows - 3 ? rows - 3 : i);
@@ -256,8 +256,10 @@ __device__ __forceinline__ T grid_interp(const P* tab, int rows, int cols, T us,
 #pragma unroll
     for (int b = 0; b < 4; ++b) g[4 * a + b] = (T)r[b];
   }
-  asm("" : "+v"(g[0]), "+v"(g[1]), "+v"(g[2]), "+v"(g[3]), "+v"(g[4]), "+v"(g[5]), "+v"(g[6]), "+v"(g[7]));
-  asm("" : "+v"(g[8]), "+v"(g[9]), "+v"(g[10]), "+v"(g[11]), "+v"(g[12]), "+v"(g[13]), "+v"(g[14]), "+v"(g[15]));
+  if constexpr (kTogether) {
+    asm("" : "+v"(g[0]), "+v"(g[1]), "+v"(g[2]), "+v"(g[3]), "+v"(g[4]), "+v"(g[5]), "+v"(g[6]), "+v"(g[7]));
+    asm("" : "+v"(g[8]), "+v"(g[9]), "+v"(g[10]), "+v"(g[11]), "+v"(g[12]), "+v"(g[13]), "+v"(g[14]), "+v"(g[15]));
+  }
   T acc = T(0);
 #pragma unroll
   for (int a = 0; a < 4; ++a) {
@@ -389,7 +391,7 @@ __device__ __forceinline__ void sample_pair64(const CdfView& c, double s_chi, ui
   ux = fmin(ux, (double)(c.cols64 - 1));
   double us = (s_chi - c.s0_64) * c.inv_hs64;
   us = fmin(fmax(us, 0.0), (double)(c.rows64 - 1));
-  double q = grid_interp<double, double>(c.f64, c.rows64, c.cols64, us, ux);
+  double q = grid_interp<double, double, false>(c.f64, c.rows64, c.cols64, us, ux);
   q = fmin(q, 0.0);
   const double qq = x > 0.0 ? -q : q;
   xi = 1.0 / (1.0 + exp(-qq));
