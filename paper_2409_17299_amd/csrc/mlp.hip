@@ -127,30 +127,33 @@ struct InferParams {
 
 // For h = 0, 1 and slot = 0..31 (feature f = phi(slot / 8, h, slot % 8)):
 // l1[h][slot] = b1[f], l3[h][slot] = w3[f].  The whole block calls this (it
-// synchronises).
-__device__ __forceinline__ void load_infer_params(const MlpPacked* W, int lane, InferParams& P, float (*l1)[32],
-                                                  float (*l3)[32]) {
+// synchronises).  The weights of layer 1 and the biases go through LDS (p1): read
+// by every lane from memory they are 32 loads of 16 bytes a lane, 3 us of a
+// wave's start, which calls of 1e5 samples, 32 a wave, do not hide.
+__device__ __forceinline__ void load_infer_params(const MlpPacked* W, int lane, InferParams& P, float4* p1,
+                                                  float (*l1)[32], float (*l3)[32]) {
   const int h = lane >> 5;
+  if (threadIdx.x < 64) {
+    const int hh = threadIdx.x >> 5, q = threadIdx.x & 31, f = mlp_phi(q >> 3, hh, q & 7);
+    p1[threadIdx.x] = W->p1[threadIdx.x];
+    l1[hh][q] = W->p1[f].z;
+    l3[hh][q] = W->w3[f];
+  }
 #pragma unroll
   for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
     for (int s = 0; s < 4; ++s) P.w2[mt][s] = frag_load(W->w2a[mt][s][lane]);
+  P.b3 = W->b3;
+  __syncthreads();
 #pragma unroll
   for (int s = 0; s < 4; ++s)
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const float4 q = W->p1[mlp_phi(s, h, i)];
+      const float4 q = p1[mlp_phi(s, h, i)];
       P.w1a[s * 8 + i] = q.x;
       P.w1b[s * 8 + i] = q.y;
       P.b2[s >> 1][(s & 1) * 8 + i] = q.w;
     }
-  P.b3 = W->b3;
-  if (threadIdx.x < 64) {
-    const int hh = threadIdx.x >> 5, q = threadIdx.x & 31, f = mlp_phi(q >> 3, hh, q & 7);
-    l1[hh][q] = W->p1[f].z;
-    l3[hh][q] = W->w3[f];
-  }
-  __syncthreads();
 }
 
 // This half-wave's part of the output for the sample of lane l and l + 32
@@ -238,9 +241,10 @@ __device__ __forceinline__ float forward_infer(const InferParams& P, const float
 __global__ void __launch_bounds__(kMlpThreads, 2) k_mlp_forward(const MlpPacked* W, const float* x, float* y,
                                                                 int64_t n) {
   __shared__ __align__(16) float l1[2][32], l3[2][32];
+  __shared__ float4 p1[kH];
   const int lane = threadIdx.x & 63;
   InferParams P;
-  load_infer_params(W, lane, P, l1, l3);
+  load_infer_params(W, lane, P, p1, l1, l3);
   const float4* l1h = reinterpret_cast<const float4*>(l1[lane >> 5]);
   const float4* l3h = reinterpret_cast<const float4*>(l3[lane >> 5]);
   const int64_t nw = (int64_t)gridDim.x * (kMlpThreads / 64);
@@ -261,9 +265,10 @@ __global__ void __launch_bounds__(kMlpThreads, 2) k_mlp_sample(const MlpPacked* 
                                                               const float* chi, const uint32_t* k, float* delta,
                                                               int64_t n) {
   __shared__ __align__(16) float l1[2][32], l3[2][32];
+  __shared__ float4 p1[kH];
   const int lane = threadIdx.x & 63;
   InferParams P;
-  load_infer_params(W, lane, P, l1, l3);
+  load_infer_params(W, lane, P, p1, l1, l3);
   const float4* l1h = reinterpret_cast<const float4*>(l1[lane >> 5]);
   const float4* l3h = reinterpret_cast<const float4*>(l3[lane >> 5]);
   const int64_t nw = (int64_t)gridDim.x * (kMlpThreads / 64);
