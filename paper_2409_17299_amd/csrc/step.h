@@ -277,8 +277,8 @@ struct ResampleArgs {
 };
 
 // One launch compacts up to three species: block b works on species k for
-// first_block[k] <= b < first_block[k + 1] (a species that keeps everything has
-// no blocks).
+// first_block[k] <= b < first_block[k + 1] (a species without a filter or target
+// has no blocks; the blocks of one that keeps everything return at once).
 template <typename T>
 struct ResampleLaunch {
   ResampleArgs<T> a[3];

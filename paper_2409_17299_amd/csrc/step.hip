@@ -1880,7 +1880,7 @@ __global__ void __launch_bounds__(kStepThreads, sizeof(T) == 4 ? kStepWavesPerSi
 // weight w_th per species; a particle lighter than w_th stays with probability
 // w / w_th and then weighs w_th, heavier ones stay as they are).  w_th solves
 // sum_i min(1, w_i / w_th) = n_target over the particles that pass the filter;
-// the host finds it from the sums below (api.cpp).
+// the kernels below find it on the device, and the host queues them (api.cpp).
 
 // |k|^2 >= e_min^2 in FP64, summed left to right without contraction
 template <typename T>
@@ -2045,8 +2045,9 @@ __global__ void __launch_bounds__(kLevelThreads) k_level_step(LevelArgs<T> a, in
 // words of that pass.  Waiting for them is bounded (a.wait): nothing promises
 // that all blocks are on the chip together, so one that has waited too long
 // leaves and says so, the others follow without waiting in turn, and the host
-// goes on from the last pass that was completed, with the two kernels.  State and sums cross the XCDs' L2s: they are written and read
-// with agent-scope atomics only.
+// goes on from the last pass that was completed, with the two kernels.  State
+// and sums cross the XCDs' L2s: they are written and read with agent-scope
+// atomics only.
 // A pass is a few LDS reads per thread, five trips through memory one after
 // another and two trees, 9 us against 21 of the two launches: 8e6 particles, nine
 // passes, 185 -> 103 us (a fence of the chip's L2s at each barrier made it 185
