@@ -788,8 +788,8 @@ __device__ __forceinline__ uint32_t wq_take(WaveQueue& q, const WqPlan& p, bool 
 // the finished particle's optical depth.  A particle without events is never
 // replayed.  When the pool runs out, the wave stops writing, raises the
 // overflow flag and the direct write kernel does the launch's writes; every
-// wave still adds up the bytes it would have needed, so that the host can
-// grow the pool.
+// wave still adds up what it would have needed, so that the host can grow the
+// pool.
 // Wave-uniform state of one wave's log, kept in 32-bit words (scalar
 // registers are scarce in the count kernel).
 struct LogWriter {
